@@ -51,6 +51,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
 
   const Slot fresh{~0ull, EMPTY, 0xFFFFFFFFu};
   for (int i = tid; i < LightCfg<NT>::SLOTS; i += NT) S.table[i] = fresh;
+  for (int i = tid; i < 2 * LightCfg<NT>::MARK_WORDS; i += NT) S.mark[0][i] = make_uint2(0, 0);
   if (tid == 0) {
     reset_ctr(S.fc[0]); reset_ctr(S.fc[1]);
     if (is_init) foff[0] = 0;
@@ -80,7 +81,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
     const long long o0 = uni(foff[ctx.nf - 1]), o1 = uni(foff[ctx.nf]);
     ctx.in_off = o0; ctx.n_in = (int)(o1 - o0);
   }
-  ctx.pending_clear = 0; ctx.par = 0; ctx.tok_valid = false; ctx.scan_ready = false;
+  ctx.pending_clear = 0; ctx.par = 0; ctx.tok_valid = false; ctx.n_arcs = 0; ctx.n_dead = 0;
   __syncthreads();
   // Seal the lane's state as the next snapshot of this call.  With snapshot blocks the lattice
   // records not handed out yet move into the snapshot's block, in the caller's form (the lane
@@ -167,7 +168,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
     ctx.status = uni(S.status); ctx.nf = uni(S.nf); ctx.n_in = uni(S.n_in); ctx.max_pre = uni(S.max_pre); ctx.max_post = uni(S.max_post);
     ctx.iters_max = uni(S.iters_max); ctx.in_off = uni(S.in_off); ctx.hist_used = uni(S.hist_used); ctx.lat_room = uni(S.lat_room);
     ctx.lat_total = uni(S.lat_total); ctx.lat_pos = uni(S.lat_pos); ctx.arcs_expanded = uni(S.arcs_expanded);
-    ctx.tok_valid = false; ctx.scan_ready = false;
+    ctx.tok_valid = false;
     __syncthreads();                                  // all have read the state before the next general frame rewrites it
   };
   const int nframes = is_init ? 1 : lp.n_frames;
@@ -180,7 +181,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
       const float *ll = is_init ? nullptr : lp.ll + (size_t)f * (size_t)lp.stride;
       const float *ll_next = (!is_init && f + 1 < nframes) ? ll + lp.stride : nullptr;
       bool done = false;
-      if (light_ok && (is_init || ctx.n_in <= LightCfg<NT>::NIN_MAX))
+      if (light_ok && (is_init || ctx.n_in <= LightCfg<NT>::CLAIM_LIMIT))
         done = light_frame<NT>(D, S, ctx, ll, ll_next, is_init != 0, lp.chan);
       if (!done) {
 #ifdef WFST_PHASE_TIMING

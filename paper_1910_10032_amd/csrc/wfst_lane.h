@@ -65,60 +65,52 @@ __device__ __forceinline__ void lds_barrier() {
 template <int NT> struct LightCfg {
   static constexpr int SLOTS = NT >= 1024 ? 4096 : 2048;   // state table
   static constexpr int HBITS = NT >= 1024 ? 12 : 11;
-  static constexpr int CLAIM_LIMIT = SLOTS * 3 / 4;        // states touched in a frame
-  static constexpr int NIN_MAX = SLOTS / 2;                // tokens a light frame starts from
-  static constexpr int QCAP = SLOTS;                       // queue entries: claims + re-expansion requests
-  static constexpr int ECAP = NT >= 1024 ? 1536 : 768;     // epsilon arcs parked in LDS
-  static constexpr int EXP_U = NT >= 512 ? 4 : 8;          // arcs per thread and round of the expansion
+  static constexpr int CLAIM_LIMIT = SLOTS * 3 / 4;        // states reached in a frame = tokens of the next one
+  static constexpr int TILE = NT * 4;                      // emitting arcs expanded together, four per thread
+  static constexpr int ARCS = TILE * 2;                    // emitting arcs of a frame
+  static constexpr int MARK_WORDS = ARCS / 32;
+  static constexpr int ECAP = NT >= 1024 ? 2560 : 1280;    // epsilon arcs listed in a frame
+  static constexpr uint32_t MAX_PROBES = 256;              // of the table (a frame that fills it is given up)
 };
-// queue entry (16 bits): slot | LQ_DUP (a re-expansion request for a state claimed earlier)
-constexpr uint32_t LQ_DUP = 0x8000u, LQ_SLOT = 0x7FFFu;
-// Slot::aux of the light table:  [31:16] first parked epsilon arc of the state
-//                                [15:12] its epsilon out-degree
-//                                [11:0]  its emitting out-degree; after contraction: index of
-//                                        the kept token in the new frame, POS_NONE if dropped
-constexpr uint32_t POS_MASK = 0xFFFu, POS_NONE = 0xFFFu;
-// a round's counter: [63:42] states claimed, [41:21] entries appended that have epsilon arcs to
-// relax (claims of such states, re-expansion requests), [20] give the frame up, [19:0] entries appended
-constexpr unsigned long long CNT_RESTART = 1ull << 20;
-constexpr uint32_t CNT_ENTRIES = 0xFFFFFu;
-constexpr int CNT_EPS_SHIFT = 21, CNT_CLAIM_SHIFT = 42;
-constexpr uint32_t CNT_EPS = 0x1FFFFFu;
-constexpr uint32_t F_NAN = 1, F_TOKOVF = 2, F_LATOVF = 4, F_RESTART = 8;
+// Slot::aux of the light table: degree info of the state << 16 | index of its token in the new
+// frame (POS_NONE: cut by max-active)
+constexpr uint32_t POS_NONE = 0xFFFFu;
+constexpr uint32_t TOK_DEAD = 0x80000000u;    // in LaneShared::tok: the state has no emitting arc (it takes one arc position all the same)
+constexpr uint32_t EA_AGAIN = 0x8000u, EA_SLOT = 0x7FFFu;  // epsilon entry: listed before, its source has improved since
+// What a stage allots, one 64-bit counter: [63] give the frame up, [62:32] arc positions of the
+// next frame, [31:16] epsilon arcs listed, [15:0] states claimed
+constexpr unsigned long long CNT_RESTART = 1ull << 63;
+constexpr int CNT_ARC_SHIFT = 32, CNT_EPS_SHIFT = 16;
+constexpr uint32_t CNT_ARCS = 0x7FFFFFFFu;
+constexpr uint32_t F_NAN = 1, F_TOKOVF = 2, F_LATOVF = 4;
 constexpr uint32_t KEY_NONE = 0xFFFFFFFFu;
 constexpr uint32_t KEY_PINF = 0xFF800000u;    // okey(+inf)
 
-// An epsilon arc parked in LDS by the thread that claimed its source state.
-struct __align__(16) ENote {
-  float w; uint32_t arc;
-  uint32_t dest;             // dest handle | HAS_EPS
-  uint32_t dinfo_dslot;      // degree info of the dest << 16 | slot of the dest once a candidate over
-                             // this arc has entered the table (0xFFFF before)
-};
-
 // Counters of one frame.  Two sets are used alternately, so that a frame can start while the
 // previous frame's values are still being read; the set not in use is reset in between.
-struct FrameCtr {
-  // per closure round: states claimed | entries with epsilon work | CNT_RESTART | entries appended.  A round's
-  // counter is final at the round's barrier (the next round uses another one), so every thread
-  // reads the same value there - also the request to give the frame up.
+struct __align__(16) FrameCtr {
+  // what the insertion and the closure rounds allot.  A round's counter is final at the round's
+  // barrier (the next round uses another one), so every thread reads the same value there - also
+  // the request to give the frame up.
   unsigned long long cnt[3];
-  uint32_t best, flags, auxn, nout, latn, enote_n, nvalid, kmin, kmax, eps_arcs;
+  unsigned long long sel;      // after a selection: arc positions << 32 | tokens kept
+  uint32_t flags, latn, dead, again;   // (read together at the end of the frame)
+  uint32_t best, kmin, kmax, pad;
 };
 __device__ __forceinline__ void reset_ctr(FrameCtr &c) {
-  c.cnt[0] = 0; c.cnt[1] = 0; c.cnt[2] = 0;
-  c.best = KEY_NONE; c.flags = 0; c.auxn = 0; c.nout = 0; c.latn = 0; c.enote_n = 0; c.nvalid = 0;
-  c.kmin = 0xFFFFFFFFu; c.kmax = 0; c.eps_arcs = 0;
+  c.cnt[0] = 0; c.cnt[1] = 0; c.cnt[2] = 0; c.sel = 0;
+  c.best = KEY_NONE; c.flags = 0; c.latn = 0; c.dead = 0; c.again = 0;
+  c.kmin = 0xFFFFFFFFu; c.kmax = 0;
 }
 
 // State of a lane that every thread of its workgroup holds in registers (all values uniform).
 struct LaneCtx {
   int status, nf, n_in, max_pre, max_post, iters_max;
   long long in_off, hist_used, lat_room, lat_total, lat_pos, lat_head, lat_head_pos, arcs_expanded;
-  uint32_t pending_clear;    // queue entries of the last light frame whose table slots are still to be cleared
-  int par;                   // counter set the next light frame uses
-  bool tok_valid;            // the LDS token list holds the frame the next one starts from
-  bool scan_ready;           // ... and the prefix sums of its first tile's out-degrees are in LDS too
+  uint32_t pending_clear;    // states claimed by the last light frame, whose table slots are still to be cleared
+  int par;                   // counter set (and set of first-arc marks) the next light frame uses
+  bool tok_valid;            // the LDS token list holds the frame the next one starts from:
+  uint32_t n_arcs, n_dead;   // arc positions its tokens take, and how many of them belong to tokens without an emitting arc
 #ifdef WFST_PHASE_TIMING
   unsigned long long tlast;
 #endif
@@ -258,11 +250,15 @@ struct LaneShared {
 #endif
   // -- light frame
   FrameCtr fc[2];
-  uint32_t tok_h[LightCfg<NT>::CLAIM_LIMIT];   // kept tokens of the last frame = queue of the next:
-  float tok_c[LightCfg<NT>::CLAIM_LIMIT];      //   state handle | HAS_EPS, cost,
-  uint16_t tok_i[LightCfg<NT>::CLAIM_LIMIT];   //   degree info
-  uint16_t lq[LightCfg<NT>::QCAP];             // the frame's queue: claimed slots and re-expansion requests
-  ENote enote[LightCfg<NT>::ECAP];             // epsilon arcs of the claimed states
+  uint2 tok[LightCfg<NT>::CLAIM_LIMIT];        // kept tokens of the last frame = queue of the next: state handle | TOK_DEAD, cost
+  uint16_t tok_a[LightCfg<NT>::CLAIM_LIMIT];   //   position of the token's first arc among the frame's arcs
+  uint2 mark[2][LightCfg<NT>::MARK_WORDS];     // arc positions at which a token's arcs begin (bits), and their number in the words before
+  uint32_t list_dead;
+  uint16_t lq[LightCfg<NT>::CLAIM_LIMIT];      // claimed slots, in the order of their tokens
+  uint32_t ea_r[LightCfg<NT>::ECAP];           // epsilon arcs to relax: arc,
+  float ea_w[LightCfg<NT>::ECAP];              //   weight (once fetched),
+  uint16_t ea_s[LightCfg<NT>::ECAP];           //   slot of the source | EA_AGAIN,
+  uint16_t ea_d[LightCfg<NT>::ECAP];           //   slot of the destination, 0xFFFF if the candidate was beyond the cutoff
   Slot table[LightCfg<NT>::SLOTS];             // state table
 };
 
