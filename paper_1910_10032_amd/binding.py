@@ -374,7 +374,7 @@ class WfstDecoder:
         ch = np.ascontiguousarray(channels, np.int32)
         n = len(ch)
         while True:
-            out = np.zeros(max(cap, 1), LAT_DTYPE)
+            out = np.empty(max(cap, 1), LAT_DTYPE)         # (pages that no record is written to are never touched)
             offs, st = np.zeros(n + 1, np.int64), np.zeros(n, np.int32)
             info = (wfst_lattice_info_t * max(n, 1))()
             rc = lib().wfst_decode_final_lattice_batch(self.h, ch.ctypes.data, n, int(use_final), out.ctypes.data, cap,
@@ -383,8 +383,10 @@ class WfstDecoder:
                 cap = int(offs[n])
                 continue
             _check(rc, "wfst_decode_final_lattice_batch")
-            infos = [{k: getattr(info[i], k) for k, _ in wfst_lattice_info_t._fields_} for i in range(n)]
-            return out[:offs[n]].copy(), offs, infos, st
+            names = wfst_lattice_info_t._fields_
+            fields = np.frombuffer(info, np.dtype(wfst_lattice_info_t), n)
+            infos = [dict(zip([k for k, _ in names], v)) for v in fields.tolist()]
+            return out[:offs[n]], offs, infos, st
 
     def final_lattice_device(self, channel: int, use_final: bool, out_ptr: int, cap: int, noalloc: bool = False):
         """wfst_decode_final_lattice with DEVICE output (out_ptr: device address of cap records), or its

@@ -45,15 +45,17 @@ struct wfst_decoder {
   std::vector<int64_t> frames_fed;      // host mirror: rows of scores handed to the channel
   std::vector<uint32_t> stamp;          // duplicate detection within a call
   uint32_t stamp_now = 0;
-  LaneParam *d_params = nullptr;        // [max_lanes]
   WideLane *d_wide = nullptr;           // [max_lanes] lanes shared by several workgroups (lane_workgroups > 1)
-  LaneParam *h_params[PARAM_RING] = {};
+  void *h_pinned = nullptr;             // pinned: lane parameters and progress words
+  LaneParam *h_params[PARAM_RING] = {}, *d_params[PARAM_RING] = {};   // pinned [max_lanes], and its device address
   hipEvent_t param_ev[PARAM_RING] = {};
   int ring_pos = 0;
   int32_t *d_chans = nullptr;           // readout scratch [max(num_channels, max_lanes)]
   std::vector<int32_t> staged_chans;    // what d_chans currently holds
   PathOut *d_pathout = nullptr;
   void *d_stage = nullptr; size_t stage_bytes = 0;
+  void *h_pin = nullptr; size_t pin_bytes = 0;   // pinned host memory that kernels write small results into
+  void *d_pin = nullptr;                // its device address
   uint32_t *fl_te = nullptr;            // final-lattice scratch [num_channels][hist_cap]: extra cost of every kept token
   long long *fl_rs = nullptr;           // [num_channels][max_frames + 3]: first lattice record of every frame
   LatticeInfoDev *fl_info = nullptr;    // [num_channels]
@@ -63,7 +65,7 @@ struct wfst_decoder {
   hipEvent_t last_advance = nullptr;    // recorded behind the last advance call
   bool have_last_advance = false;
   hipStream_t side_stream = nullptr;    // snapshot readouts run here, beside the decoding
-  long long *h_sealed = nullptr;        // pinned [max_lanes]: id of the last snapshot each lane sealed
+  long long *h_sealed = nullptr;        // [max_lanes], in h_pinned: id of the last snapshot each lane sealed
   int64_t next_snap_id = 1;
   struct SnapCall { int64_t id0; int32_t n_snaps, n_lanes; hipStream_t stream; };
   std::deque<SnapCall> snap_calls;      // the advance calls that seal snapshots, newest last
@@ -120,6 +122,19 @@ int ensure_stage(wfst_decoder *d, size_t bytes) {
   return 0;
 }
 
+// Pinned host memory for results that a kernel writes straight to the host: what a readout waits
+// for is then one kernel, not a kernel and a chain of copies.  No kernel may be using it.
+int ensure_pinned(wfst_decoder *d, size_t bytes) {
+  if (bytes <= d->pin_bytes) return 0;
+  if (d->h_pin) HIP_TRY(hipHostFree(d->h_pin));
+  d->h_pin = nullptr; d->d_pin = nullptr; d->pin_bytes = 0;
+  size_t want = std::max<size_t>(bytes, 1 << 16);
+  HIP_TRY(hipHostMalloc(&d->h_pin, want));
+  HIP_TRY(hipHostGetDevicePointer(&d->d_pin, d->h_pin, 0));
+  d->pin_bytes = want;
+  return 0;
+}
+
 int check_channels(wfst_decoder *d, const int32_t *channels, int32_t n, bool need_init) {
   if (!channels && n > 0) return WFST_E_INVALID_ARG;
   if (++d->stamp_now == 0) { std::fill(d->stamp.begin(), d->stamp.end(), 0u); d->stamp_now = 1; }
@@ -133,7 +148,7 @@ int check_channels(wfst_decoder *d, const int32_t *channels, int32_t n, bool nee
   return 0;
 }
 
-// Stage lane parameters through a pinned ring and launch the lane kernel.  wide: several
+// Put the lane parameters into a pinned ring and launch the lane kernel.  wide: several
 // workgroups per lane (only for calls without snapshots whose lanes x workgroups fit the device
 // at one workgroup per compute unit, so that all of them are resident and can wait for each other).
 int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init, hipStream_t stream, bool wide = false) {
@@ -141,10 +156,9 @@ int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init,
   if (n == 0) return 0;
   const int slot = d->ring_pos;
   d->ring_pos = (d->ring_pos + 1) % PARAM_RING;
-  HIP_TRY(hipEventSynchronize(d->param_ev[slot]));           // its previous copy has been consumed
+  HIP_TRY(hipEventSynchronize(d->param_ev[slot]));           // the launch that read it is over
   std::memcpy(d->h_params[slot], lp.data(), sizeof(LaneParam) * (size_t)n);
-  HIP_TRY(hipMemcpyAsync(d->d_params, d->h_params[slot], sizeof(LaneParam) * (size_t)n, hipMemcpyHostToDevice, stream));
-  HIP_TRY(hipEventRecord(d->param_ev[slot], stream));
+  const LaneParam *params = d->d_params[slot];               // (the kernel reads them where they are: no copy in front of it)
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (d->profiling && !is_init) {
     HIP_TRY(hipEventCreate(&e0)); HIP_TRY(hipEventCreate(&e1));
@@ -156,20 +170,22 @@ int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init,
   if (wide) {
     const int G = std::min(d->cfg.lane_workgroups, d->num_cus / n);
     hipLaunchKernelGGL(k_zero_wide, dim3((n + 63) / 64), dim3(64), 0, stream, d->d_wide, n);
-    hipLaunchKernelGGL(k_advance_wide<1024>, dim3(n * G), dim3(1024), 0, stream, d->dev, (const LaneParam *)d->d_params, d->d_wide, G);
+    hipLaunchKernelGGL(k_advance_wide<1024>, dim3(n * G), dim3(1024), 0, stream, d->dev, params, d->d_wide, G);
     HIP_TRY(hipGetLastError());
+    HIP_TRY(hipEventRecord(d->param_ev[slot], stream));
     if (e0) { HIP_TRY(hipEventRecord(e1, stream)); d->prof_events.push_back({e0, e1}); }
     return 0;
   }
   int threads = d->cfg.lane_threads;
   if (threads == 0) threads = n <= d->num_cus ? 1024 : NT;
   if (threads == 1024)
-    hipLaunchKernelGGL(k_advance<1024>, dim3(n), dim3(1024), 0, stream, d->dev, (const LaneParam *)d->d_params, is_init);
+    hipLaunchKernelGGL(k_advance<1024>, dim3(n), dim3(1024), 0, stream, d->dev, params, is_init);
   else if (threads == 256)
-    hipLaunchKernelGGL(k_advance<256>, dim3(n), dim3(256), 0, stream, d->dev, (const LaneParam *)d->d_params, is_init);
+    hipLaunchKernelGGL(k_advance<256>, dim3(n), dim3(256), 0, stream, d->dev, params, is_init);
   else
-    hipLaunchKernelGGL(k_advance<NT>, dim3(n), dim3(NT), 0, stream, d->dev, (const LaneParam *)d->d_params, is_init);
+    hipLaunchKernelGGL(k_advance<NT>, dim3(n), dim3(NT), 0, stream, d->dev, params, is_init);
   HIP_TRY(hipGetLastError());
+  HIP_TRY(hipEventRecord(d->param_ev[slot], stream));
   if (e0) { HIP_TRY(hipEventRecord(e1, stream)); d->prof_events.push_back({e0, e1}); }
   return 0;
 }
@@ -389,7 +405,6 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
   if (!rc) rc = dev_alloc(d, &D.aux, nl * (size_t)D.auxcap);
   if (!rc) rc = dev_alloc(d, &D.dkey, nl * (size_t)D.tokcap);
   if (!rc) rc = dev_alloc(d, &D.dslot, nl * (size_t)D.tokcap);
-  if (!rc) rc = dev_alloc(d, &d->d_params, nl);
   if (!rc && c.lane_workgroups > 1) rc = dev_alloc(d, &d->d_wide, nl);
   d->per_lane_bytes = (d->total_bytes - before_lanes) / (int64_t)nl;
   if (!rc) rc = dev_alloc(d, &d->d_chans, std::max(nc, nl));
@@ -415,16 +430,24 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
   }
   if (!rc) {
     bool ok = hipMemset(D.chan, 0, sizeof(ChanState) * nc) == hipSuccess;
-    for (int i = 0; ok && i < PARAM_RING; ++i)
-      ok = hipHostMalloc((void **)&d->h_params[i], sizeof(LaneParam) * nl) == hipSuccess &&
-           hipEventCreateWithFlags(&d->param_ev[i], hipEventDisableTiming) == hipSuccess;
+    // one pinned allocation: the ring of lane parameters, then the lanes' progress words
+    const size_t ring_bytes = PARAM_RING * sizeof(LaneParam) * nl;
+    void *pinned_dev = nullptr;
+    ok = ok && hipHostMalloc(&d->h_pinned, ring_bytes + sizeof(long long) * nl) == hipSuccess &&
+         hipHostGetDevicePointer(&pinned_dev, d->h_pinned, 0) == hipSuccess;
+    for (int i = 0; ok && i < PARAM_RING; ++i) {
+      d->h_params[i] = (LaneParam *)d->h_pinned + (size_t)i * nl;
+      d->d_params[i] = (LaneParam *)pinned_dev + (size_t)i * nl;
+      ok = hipEventCreateWithFlags(&d->param_ev[i], hipEventDisableTiming) == hipSuccess;
+    }
     ok = ok && hipMemset(D.snap, 0, sizeof(ChanSnap) * nc * SNAP_RING) == hipSuccess &&
          hipStreamCreateWithFlags(&d->side_stream, hipStreamNonBlocking) == hipSuccess &&
          hipEventCreateWithFlags(&d->last_advance, hipEventDisableTiming) == hipSuccess &&
-         hipHostMalloc((void **)&d->h_sealed, sizeof(long long) * nl) == hipSuccess;
+         ensure_pinned(d, (sizeof(long long) + sizeof(LatticeInfoDev)) * (std::max(nc, nl) + 1)) == 0;   // (what no call grows)
     if (ok) {
+      d->h_sealed = (long long *)((char *)d->h_pinned + ring_bytes);
+      D.lane_sealed = (long long *)((char *)pinned_dev + ring_bytes);
       std::memset(d->h_sealed, 0, sizeof(long long) * nl);
-      ok = hipHostGetDevicePointer((void **)&D.lane_sealed, d->h_sealed, 0) == hipSuccess;
     }
     if (ok) {
       hipLaunchKernelGGL(k_fill_slots, dim3(1024), dim3(256), 0, 0, D.slots, nl * (size_t)D.H);
@@ -443,14 +466,14 @@ void wfst_decode_destroy(wfst_decoder_t *d) {
   (void)hipDeviceSynchronize();
   for (void *p : d->allocs) (void)hipFree(p);
   if (d->d_stage) (void)hipFree(d->d_stage);
+  if (d->h_pin) (void)hipHostFree(d->h_pin);
   for (int i = 0; i < PARAM_RING; ++i) {
-    if (d->h_params[i]) (void)hipHostFree(d->h_params[i]);
     if (d->param_ev[i]) (void)hipEventDestroy(d->param_ev[i]);
   }
   for (auto &p : d->prof_events) { (void)hipEventDestroy(p.first); (void)hipEventDestroy(p.second); }
   if (d->side_stream) (void)hipStreamDestroy(d->side_stream);
   if (d->last_advance) (void)hipEventDestroy(d->last_advance);
-  if (d->h_sealed) (void)hipHostFree(d->h_sealed);
+  if (d->h_pinned) (void)hipHostFree(d->h_pinned);
   delete d;
 }
 
@@ -766,14 +789,20 @@ int wfst_decode_lattice_arcs_batch(wfst_decoder_t *d, const int32_t *channels, i
   }
   // offsets, copy and reset are queued back to back; the copy and the reset check the capacity
   // on the device, so the host waits only once
-  hipLaunchKernelGGL(k_lattice_offsets, dim3(1), dim3(1024), 0, st, d->dev, (const int32_t *)d->d_chans, n, d->d_offs);
+  if (sizeof(long long) * ((size_t)n + 1) > d->pin_bytes) {
+    HIP_TRY(hipStreamSynchronize(st));
+    rc = ensure_pinned(d, sizeof(long long) * ((size_t)n + 1));
+    if (rc) return rc;
+  }
+  hipLaunchKernelGGL(k_lattice_offsets, dim3(1), dim3(1024), 0, st, d->dev, (const int32_t *)d->d_chans, n, d->d_offs, (long long *)d->d_pin);
   hipLaunchKernelGGL(k_export_lattice_batch, dim3(n, 8), dim3(256), 0, st, d->dev, (const int32_t *)d->d_chans, n,
                      (const long long *)d->d_offs, dst, (long long)cap);
   hipLaunchKernelGGL(k_reset_lattice_batch, dim3((n + 255) / 256), dim3(256), 0, st, d->dev, (const int32_t *)d->d_chans, n,
                      (const long long *)d->d_offs, (long long)cap);
   HIP_TRY(hipGetLastError());
   static_assert(sizeof(long long) == sizeof(int64_t), "offset width");
-  HIP_TRY(copy_sync_on(st, offsets, d->d_offs, sizeof(long long) * ((size_t)n + 1), hipMemcpyDeviceToHost));
+  HIP_TRY(hipStreamSynchronize(st));
+  std::memcpy(offsets, d->h_pin, sizeof(long long) * ((size_t)n + 1));
   const long long total = offsets[n];
   if (total > cap) return WFST_E_CAPACITY;
   if (!out_is_device && total > 0) HIP_TRY(copy_sync_on(st, out, dst, sizeof(LatRec) * (size_t)total, hipMemcpyDeviceToHost));
@@ -819,9 +848,16 @@ int wfst_decode_snapshot_lattice_arcs(wfst_decoder_t *d, int64_t snapshot_id, co
 static int final_lattice_launch(wfst_decoder *d, int32_t n, int32_t use_final, uint32_t *te, long long te_stride, long long *rs,
                                 long long rs_stride, LatticeInfoDev *info, LatRec *dst, int64_t cap) {
   hipStream_t st = d->last_stream;
+  const size_t need = sizeof(long long) * ((size_t)n + 1) + sizeof(LatticeInfoDev) * (size_t)n;
+  if (need > d->pin_bytes) {
+    HIP_TRY(hipStreamSynchronize(st));
+    const int rc = ensure_pinned(d, need);
+    if (rc) return rc;
+  }
   hipLaunchKernelGGL(k_final_lattice_te, dim3(n), dim3(1024), 0, st, d->dev, (const int32_t *)d->d_chans, use_final, te, te_stride,
                      rs, rs_stride, info);
-  hipLaunchKernelGGL(k_final_lattice_offsets, dim3(1), dim3(1024), 0, st, (const LatticeInfoDev *)info, n, d->d_offs);
+  hipLaunchKernelGGL(k_final_lattice_offsets, dim3(1), dim3(1024), 0, st, (const LatticeInfoDev *)info, n, d->d_offs,
+                     (long long *)d->d_pin, (LatticeInfoDev *)((long long *)d->d_pin + n + 1));
   hipLaunchKernelGGL(k_final_lattice_emit, dim3(n), dim3(1024), 0, st, d->dev, (const int32_t *)d->d_chans, n, (const uint32_t *)te,
                      te_stride, (const long long *)d->d_offs, dst, (long long)cap, (const LatticeInfoDev *)info);
   HIP_TRY(hipGetLastError());
@@ -855,10 +891,10 @@ int wfst_decode_final_lattice_batch(wfst_decoder_t *d, const int32_t *channels, 
   rc = final_lattice_launch(d, n, use_final, d->fl_te, (long long)d->dev.hist_cap, d->fl_rs, (long long)d->cfg.max_frames + 3,
                             d->fl_info, dst, cap);
   if (rc) return rc;
-  std::vector<LatticeInfoDev> li((size_t)n);
-  HIP_TRY(copy_sync_on(st, li.data(), d->fl_info, sizeof(LatticeInfoDev) * (size_t)n, hipMemcpyDeviceToHost));
   static_assert(sizeof(long long) == sizeof(int64_t), "offset width");
-  HIP_TRY(copy_sync_on(st, offsets, d->d_offs, sizeof(long long) * ((size_t)n + 1), hipMemcpyDeviceToHost));
+  HIP_TRY(hipStreamSynchronize(st));
+  std::memcpy(offsets, d->h_pin, sizeof(long long) * ((size_t)n + 1));
+  const LatticeInfoDev *li = (const LatticeInfoDev *)((const long long *)d->h_pin + n + 1);
   for (int32_t i = 0; i < n; ++i) { status[i] = li[i].status; fill_info(li[i], info + i); }
   if (offsets[n] > cap) return WFST_E_CAPACITY;
   if (!out_is_device && offsets[n] > 0)
@@ -901,8 +937,8 @@ int wfst_decode_final_lattice_noalloc(wfst_decoder_t *d, int32_t channel, int32_
   rc = final_lattice_launch(d, 1, use_final, (uint32_t *)base, 0, (long long *)(base + rs_off), 0, (LatticeInfoDev *)(base + info_off),
                             (LatRec *)out, cap);
   if (rc) return rc;
-  LatticeInfoDev li;
-  HIP_TRY(copy_sync(d, &li, base + info_off, sizeof(li), hipMemcpyDeviceToHost));
+  HIP_TRY(hipStreamSynchronize(d->last_stream));
+  const LatticeInfoDev li = *(const LatticeInfoDev *)((const long long *)d->h_pin + 2);
   if (li.status != 0) return li.status;
   *n = li.arcs_kept;
   if (li.arcs_kept > cap) return WFST_E_CAPACITY;

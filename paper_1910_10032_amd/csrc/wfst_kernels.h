@@ -499,8 +499,8 @@ __global__ void k_reset_lattice(DecDev D, int ch) { D.chan[ch].lat_head = D.chan
 // Batched drain: counts of the listed channels, then one copy kernel (grid.x = channel,
 // grid.y = slices of that channel's buffer), then the reset.
 // offs[0..n]: exclusive prefix sums of the buffered record counts of the listed channels
-// (channels stopped by an overflow count as empty).  One block.
-__global__ void __launch_bounds__(1024) k_lattice_offsets(DecDev D, const int32_t *chans, int n, long long *offs) {
+// (channels stopped by an overflow count as empty), also written to pinned host memory.  One block.
+__global__ void __launch_bounds__(1024) k_lattice_offsets(DecDev D, const int32_t *chans, int n, long long *offs, long long *offs_host) {
   __shared__ long long part[1024];
   const int tid = threadIdx.x;
   const int per = (n + 1023) / 1024;
@@ -519,10 +519,10 @@ __global__ void __launch_bounds__(1024) k_lattice_offsets(DecDev D, const int32_
   }
   long long run = part[tid] - sum;
   for (int i = b; i < e; ++i) {
-    offs[i] = run;
+    offs[i] = run; offs_host[i] = run;
     run += lattice_pending(D, chans[i]);
   }
-  if (tid == 1023) offs[n] = part[1023];
+  if (tid == 1023) { offs[n] = part[1023]; offs_host[n] = part[1023]; }
 }
 __global__ void k_export_lattice_batch(DecDev D, const int32_t *chans, int n_ch, const long long *offs, LatRec *out, long long cap) {
   if (offs[n_ch] > cap) return;                       // caller's buffer too small: nothing is copied or drained
@@ -570,66 +570,33 @@ __global__ void k_snapshot_ranges(DecDev D, const int32_t *chans, int n, long lo
 // the minimum over recorded arcs a: n -> m of te(m) + extra(a); in the last frame it is the
 // token's distance to the best (final) cost.  An arc into m is kept iff te(m) + extra(a) <=
 // lattice_beam.  fp32, one rounded add per step; minima via integer atomics on the (non-
-// negative) float bits, so the result does not depend on thread order.  One workgroup.
-struct LatticeInfoDev { long long arcs_in, arcs_kept; int32_t frames, reached_final, status, pad; float best_cost, pad2; };
+// negative) float bits, so the result does not depend on thread order.
+struct LatticeInfoDev { long long arcs_in, arcs_kept; int32_t frames, reached_final, status, listed; float best_cost, pad2; };
 
-// Pass 1, one workgroup per listed channel: the extra cost te of every kept token (into the
-// channel's scratch: te one word per token, rec_start one offset per frame) and the number of
-// arcs that survive, into info[blockIdx.x].  te_stride / rs_stride: distance between the
-// scratch areas of consecutive channel ids (0: a single area, for a call on one channel).
-__global__ void __launch_bounds__(1024) k_final_lattice_te(DecDev D, const int32_t *chans, int use_final, uint32_t *te_base,
-                                                           long long te_stride, long long *rs_base, long long rs_stride,
-                                                           LatticeInfoDev *info) {
-  const int tid = threadIdx.x, NTH = 1024;
-  const int ch = chans[blockIdx.x];
-  uint32_t *te = te_base + (size_t)ch * (size_t)te_stride;
-  long long *rec_start = rs_base + (size_t)ch * (size_t)rs_stride;
-  const ChanState *cs = D.chan + ch;
-  const long long *foff = D.frame_off + (size_t)ch * (size_t)(D.max_frames + 2);
-  const HTok *hist = D.hist + (size_t)ch * (size_t)D.hist_cap;
-  const LatInt *lat_ring = D.lat + (size_t)ch * (size_t)D.lat_cap;
-  const long long lat_first = cs->lat_head % D.lat_cap, lat_cap = D.lat_cap;
-  // record i of the buffered ones (they start at ring position lat_first)
-  auto lat = [&](long long i) -> const LatInt & { return lat_ring[lat_first + i < lat_cap ? lat_first + i : lat_first + i - lat_cap]; };
+constexpr int FL_NT = 1024;
+constexpr int FL_U = 4;                       // records of a frame per thread, in registers
+constexpr int FL_TOK = 16384;                 // tokens of a frame whose te fits LDS
+constexpr int FL_WIN = 256;                   // frames whose offsets are in LDS at a time
+struct FinalShared {
+  uint32_t te[2][FL_TOK];
+  long long off[FL_WIN + 4], rs[FL_WIN + 4];
+  uint32_t changed[3], best_f, best_n, n_list;
+  unsigned long long kept;
+};
+
+// The pass with te in global memory, frame by frame: for channels with a frame that has more
+// tokens than FL_TOK, or more arcs to keep than the list of survivors holds.  Leaves every token's
+// te in te[]; returns (to thread 0) the number of arcs kept.
+template <class L>
+__device__ unsigned long long final_te_global(const DecDev &D, FinalShared &S, L lat, long long n_rec, const long long *foff, int T, long long n_tok,
+                                              uint32_t *te, const long long *rec_start, const HTok *hist, bool any_final, float best) {
+  const int tid = threadIdx.x, NTH = FL_NT;
   const uint32_t *rec = D.g.rec;
-  __shared__ uint32_t s_best_f, s_best_n, s_changed;
-  __shared__ unsigned long long s_kept;
-  const int st = cs->status;
-  const bool readable = st == 0;
-  const int T = cs->num_frames - 1;
-  const long long n_rec = cs->lat_total - cs->lat_head;
-  const long long n_tok = cs->hist_used;
-  const long long oT = T >= 0 ? foff[T] : 0;
-  const int nT = T >= 0 ? (int)(foff[T + 1] - oT) : 0;
-  if (!readable || nT == 0) {
-    if (tid == 0) { LatticeInfoDev li{n_rec, 0, T + 1, 0, readable ? E_DEAD_CHANNEL : st, 0, 0.f, 0.f}; info[blockIdx.x] = li; }
-    return;
-  }
-  if (tid == 0) { s_best_f = KEY_NONE; s_best_n = KEY_NONE; s_kept = 0; }
+  const long long oT = foff[T];
+  const int nT = (int)(foff[T + 1] - oT);
+  if (tid == 0) S.kept = 0;
   for (long long i = tid; i < n_tok; i += NTH) te[i] = 0x7F800000u;            // +inf
-  for (int f = tid; f <= T + 2; f += NTH) rec_start[f] = f > T ? n_rec : -1;
   __syncthreads();
-  // start of each frame's run of records (records are appended frame by frame)
-  for (long long i = tid; i < n_rec; i += NTH) {
-    const int f = lat(i).frame;
-    if (i == 0 || lat(i - 1).frame != f) rec_start[f] = i;
-  }
-  // best cost over the last frame
-  for (int i = tid; i < nT; i += NTH) {
-    const HTok t = hist[oT + i];
-    atomicMin(&s_best_n, okey(t.cost));
-    if (use_final) {
-      const float fc = __uint_as_float(rec[3 * (size_t)(t.handle & HMASK) + 2]);
-      if (fc != INFINITY) atomicMin(&s_best_f, okey(t.cost + fc));
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {                                   // frames without records inherit the next start
-    long long nxt = n_rec;
-    for (int f = T; f >= 0; --f) { if (rec_start[f] < 0) rec_start[f] = nxt; else nxt = rec_start[f]; }
-  }
-  const bool any_final = use_final && s_best_f != KEY_NONE;
-  const float best = key2f(any_final ? s_best_f : s_best_n);
   for (int i = tid; i < nT; i += NTH) {
     const HTok t = hist[oT + i];
     float v;
@@ -656,16 +623,16 @@ __global__ void __launch_bounds__(1024) k_final_lattice_te(DecDev D, const int32
     }
     const long long e0 = rec_start[f], e1 = rec_start[f + 1];
     for (;;) {                                      // epsilon arcs inside frame f, to the fixed point
-      if (tid == 0) s_changed = 0;
+      if (tid == 0) S.changed[0] = 0;
       __syncthreads();
       for (long long i = e0 + tid; i < e1; i += NTH) {
         const LatInt r = lat(i);
         if (!(r.src & PREV_SAME)) continue;
         const uint32_t v = __float_as_uint(__uint_as_float(ld32(&te[of + r.dst])) + r.extra);
-        if (v < atomicMin(&te[of + (r.src & ~PREV_SAME)], v)) s_changed = 1;
+        if (v < atomicMin(&te[of + (r.src & ~PREV_SAME)], v)) S.changed[0] = 1;
       }
       __syncthreads();
-      if (!s_changed) break;
+      if (!S.changed[0]) break;
       __syncthreads();
     }
   }
@@ -675,16 +642,184 @@ __global__ void __launch_bounds__(1024) k_final_lattice_te(DecDev D, const int32
     const float v = __uint_as_float(ld32(&te[foff[r.frame] + r.dst])) + r.extra;
     kept += v <= D.lattice_beam ? 1 : 0;
   }
-  if (kept) atomicAdd(&s_kept, kept);
+  if (kept) atomicAdd(&S.kept, kept);
   __syncthreads();
+  return S.kept;
+}
+
+// Pass 1, one workgroup per listed channel.  The channel's scratch: te, one word per token, and
+// rec_start, one offset per frame; te_stride / rs_stride: distance between the scratch areas of
+// consecutive channel ids (0: a single area, for a call on one channel).
+//
+// The frames are a serial chain, so what counts is the time per frame.  te of two frames lives in
+// LDS; a frame's records are in registers, requested two frames ahead; candidates beyond the
+// lattice beam are dropped at once (extra costs are not negative: nothing kept can come of them),
+// which leaves a few dozen live tokens per frame; two barriers per frame plus one per further
+// round over the epsilon arcs.  The surviving arcs are listed as they are found (in the te scratch,
+// which this form does not need), so no second pass over all records is made.
+// With te in global memory, one pass over all records to find the frames, one to count and one to
+// emit, the whole call took 2.31 ms for a 300-frame stream on the 1000-state graph, 13.6 ms for 400
+// frames of 6600 arcs and 11.8 ms for 100 utterances of 500 - 1500 frames; now 0.51, 1.71, 2.12 ms.
+__global__ void __launch_bounds__(FL_NT) k_final_lattice_te(DecDev D, const int32_t *chans, int use_final, uint32_t *te_base,
+                                                            long long te_stride, long long *rs_base, long long rs_stride,
+                                                            LatticeInfoDev *info) {
+  __shared__ FinalShared S;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int ch = chans[blockIdx.x];
+  uint32_t *list = te_base + (size_t)ch * (size_t)te_stride;
+  long long *rec_start = rs_base + (size_t)ch * (size_t)rs_stride;
+  const ChanState *cs = D.chan + ch;
+  const long long *foff = D.frame_off + (size_t)ch * (size_t)(D.max_frames + 2);
+  const HTok *hist = D.hist + (size_t)ch * (size_t)D.hist_cap;
+  const LatInt *lat_ring = D.lat + (size_t)ch * (size_t)D.lat_cap;
+  const long long lat_first = cs->lat_head % D.lat_cap, lat_cap = D.lat_cap;
+  // record i of the buffered ones (they start at ring position lat_first)
+  auto lat = [&](long long i) -> const LatInt & { return lat_ring[lat_first + i < lat_cap ? lat_first + i : lat_first + i - lat_cap]; };
+  const uint32_t *rec = D.g.rec;
+  const int st = cs->status;
+  const bool readable = st == 0;
+  const int T = cs->num_frames - 1;
+  const long long n_rec = cs->lat_total - cs->lat_head;
+  const long long n_tok = cs->hist_used;
+  const long long oT = T >= 0 ? foff[T] : 0;
+  const int nT = T >= 0 ? (int)(foff[T + 1] - oT) : 0;
+  if (!readable || nT == 0) {
+    if (tid == 0) { LatticeInfoDev li{n_rec, 0, T + 1, 0, readable ? E_DEAD_CHANNEL : st, 0, 0.f, 0.f}; info[blockIdx.x] = li; }
+    return;
+  }
+  if (tid == 0) { S.best_f = KEY_NONE; S.best_n = KEY_NONE; S.n_list = 0; S.changed[0] = 0; S.changed[1] = 0; S.changed[2] = 0; }
+  // where each frame's run of records starts (they are appended frame by frame), by bisection
+  for (int f = tid; f <= T + 2; f += FL_NT) {
+    long long lo = 0, hi = n_rec;
+    while (lo < hi) {
+      const long long mid = (lo + hi) >> 1;
+      if (lat(mid).frame < f) lo = mid + 1; else hi = mid;
+    }
+    rec_start[f] = lo;
+  }
+  __syncthreads();
+  // best cost over the last frame
+  {
+    uint32_t bn = KEY_NONE, bf = KEY_NONE;
+    for (int i = tid; i < nT; i += FL_NT) {
+      const HTok t = hist[oT + i];
+      bn = min(bn, okey(t.cost));
+      if (use_final) {
+        const float fc = __uint_as_float(rec[3 * (size_t)(t.handle & HMASK) + 2]);
+        if (fc != INFINITY) bf = min(bf, okey(t.cost + fc));
+      }
+    }
+    bn = wave_min_u32(bn); bf = wave_min_u32(bf);
+    if (lane == 0) { atomicMin(&S.best_n, bn); atomicMin(&S.best_f, bf); }
+  }
+  __syncthreads();
+  const bool any_final = use_final && S.best_f != KEY_NONE;
+  const float best = key2f(any_final ? S.best_f : S.best_n);
+  const float beam = D.lattice_beam;
+  bool in_lds = cs->max_post <= FL_TOK && n_rec < 0xFFFFFFFFll;
+  if (in_lds) {
+    for (int i = tid; i < nT; i += FL_NT) {
+      const HTok t = hist[oT + i];
+      float v;
+      if (any_final) {
+        const float fc = __uint_as_float(rec[3 * (size_t)(t.handle & HMASK) + 2]);
+        v = fc != INFINITY ? (t.cost + fc) - best : INFINITY;
+      } else {
+        v = t.cost - best;
+      }
+      S.te[T & 1][i] = __float_as_uint(v);
+    }
+    int w0 = 0;                                     // first frame of the window of offsets
+    auto load_window = [&](int top) {               // (frames top + 1 and below)
+      __syncthreads();
+      w0 = max(0, top + 2 - FL_WIN);
+      for (int i = tid; i < FL_WIN + 4; i += FL_NT) {
+        const int f = w0 + i;
+        S.off[i] = f <= T + 1 ? foff[f] : 0;
+        S.rs[i] = f <= T + 2 ? rec_start[f] : n_rec;
+      }
+      __syncthreads();
+    };
+    load_window(T);
+    struct Rec { float extra; uint32_t dst, src; };
+    struct Recs { Rec r[FL_U]; };
+    auto request = [&](int f, Recs &q) {            // the records of frame f that this thread holds in registers
+      const long long a = f >= 0 ? S.rs[f - w0] : 0, b = f >= 0 ? S.rs[f + 1 - w0] : 0;
+#pragma unroll
+      for (int u = 0; u < FL_U; ++u) {
+        const long long i = a + u * FL_NT + tid;
+        if (i < b) { const LatInt &l = lat(i); q.r[u].extra = l.extra; q.r[u].dst = l.dst; q.r[u].src = l.src; }
+      }
+    };
+    uint32_t round = 0;                             // rounds over epsilon arcs so far, all frames
+    auto step = [&](int f, const Recs &q) {
+      const long long a = S.rs[f - w0], b = S.rs[f + 1 - w0];
+      const int n_below = f > 0 ? (int)(S.off[f - w0] - S.off[f - 1 - w0]) : 0;
+      uint32_t *cur = S.te[f & 1], *below = S.te[(f & 1) ^ 1];
+      for (int i = tid; i < n_below; i += FL_NT) below[i] = 0x7F800000u;
+      auto each = [&](auto fn) {
+#pragma unroll
+        for (int u = 0; u < FL_U; ++u) {
+          const long long i = a + u * FL_NT + tid;
+          if (a + u * FL_NT < b) fn(i < b, i, q.r[u]);
+        }
+#pragma unroll 1
+        for (long long i0 = a + FL_U * FL_NT; i0 < b; i0 += FL_NT) {
+          const long long i = i0 + tid;
+          Rec r{0.f, 0, 0};
+          if (i < b) { const LatInt &l = lat(i); r = Rec{l.extra, l.dst, l.src}; }
+          fn(i < b, i, r);
+        }
+      };
+      for (;;) {                                    // epsilon arcs inside the frame, to the fixed point
+        if (tid == 0) S.changed[(round + 1) % 3] = 0;
+        each([&](bool mine, long long, const Rec &r) {
+          if (!mine || !(r.src & PREV_SAME)) return;
+          const float v = __uint_as_float(cur[r.dst]) + r.extra;
+          if (v <= beam && __float_as_uint(v) < atomicMin(&cur[r.src & ~PREV_SAME], __float_as_uint(v))) S.changed[round % 3] = 1;
+        });
+        lds_barrier();
+        if (!uni(S.changed[round++ % 3])) break;
+      }
+      each([&](bool mine, long long i, const Rec &r) {
+        const float v = mine ? __uint_as_float(cur[r.dst]) + r.extra : INFINITY;
+        const bool keep = v <= beam;
+        if (keep && !(r.src & PREV_SAME)) atomicMin(&below[r.src], __float_as_uint(v));
+        const unsigned long long m = __ballot(keep);
+        if (m) {
+          uint32_t p = 0;
+          if (lane == 0) p = atomicAdd(&S.n_list, (uint32_t)__popcll(m));
+          p = uni(p) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+          if (keep && (long long)p < n_tok) list[p] = (uint32_t)i;
+        }
+      });
+      lds_barrier();
+    };
+    Recs q0, q1, q2;
+    request(T, q0); request(T - 1, q1);
+    for (int f = T; f >= 0;) {
+      if (f < w0 + 6 && w0 > 0) load_window(f);     // (three steps, each looking three frames down)
+      request(f - 2, q2); step(f, q0); --f;
+      if (f < 0) break;
+      request(f - 2, q0); step(f, q1); --f;
+      if (f < 0) break;
+      request(f - 2, q1); step(f, q2); --f;
+    }
+    if ((long long)S.n_list > n_tok) in_lds = false;        // (more survivors than the list holds)
+    __syncthreads();
+  }
+  unsigned long long kept = S.n_list;
+  if (!in_lds) kept = final_te_global(D, S, lat, n_rec, foff, T, n_tok, list, rec_start, hist, any_final, best);
   if (tid == 0) {
-    LatticeInfoDev li{n_rec, (long long)s_kept, T + 1, any_final ? 1 : 0, 0, 0, best, 0.f};
+    LatticeInfoDev li{n_rec, (long long)kept, T + 1, any_final ? 1 : 0, 0, in_lds ? 1 : 0, best, 0.f};
     info[blockIdx.x] = li;
   }
 }
 
-// offs[0..n]: exclusive prefix sums of the kept-arc counts of pass 1 (one block).
-__global__ void __launch_bounds__(1024) k_final_lattice_offsets(const LatticeInfoDev *info, int n, long long *offs) {
+// offs[0..n]: exclusive prefix sums of the kept-arc counts of pass 1 (one block); they and the
+// channels' results also go straight to pinned host memory.
+__global__ void __launch_bounds__(1024) k_final_lattice_offsets(const LatticeInfoDev *info, int n, long long *offs, long long *offs_host,
+                                                                LatticeInfoDev *info_host) {
   __shared__ long long part[1024];
   const int tid = threadIdx.x;
   const int per = (n + 1023) / 1024;
@@ -700,8 +835,12 @@ __global__ void __launch_bounds__(1024) k_final_lattice_offsets(const LatticeInf
     __syncthreads();
   }
   long long run = part[tid] - sum;
-  for (int i = b; i < e; ++i) { offs[i] = run; run += info[i].status == 0 ? info[i].arcs_kept : 0; }
-  if (tid == 1023) offs[n] = part[1023];
+  for (int i = b; i < e; ++i) {
+    const LatticeInfoDev li = info[i];
+    offs[i] = run; offs_host[i] = run; info_host[i] = li;
+    run += li.status == 0 ? li.arcs_kept : 0;
+  }
+  if (tid == 1023) { offs[n] = part[1023]; offs_host[n] = part[1023]; }
 }
 
 // Pass 2: the surviving arcs of listed channel blockIdx.x, in the caller's form, at out[offs[blockIdx.x] ..).
@@ -719,11 +858,20 @@ __global__ void __launch_bounds__(1024) k_final_lattice_emit(DecDev D, const int
   const long long lat_first = cs->lat_head % D.lat_cap, lat_cap = D.lat_cap;
   const long long n_rec = cs->lat_total - cs->lat_head;
   LatRec *dst = out + offs[blockIdx.x];
+  auto lat = [&](long long i) -> const LatInt & { return lat_ring[lat_first + i < lat_cap ? lat_first + i : lat_first + i - lat_cap]; };
+  if (info[blockIdx.x].listed) {                    // te[] holds the numbers of the surviving records
+    const long long n = info[blockIdx.x].arcs_kept;
+    for (long long i = tid; i < n; i += NTH) {
+      const LatInt &r = lat((long long)te[i]);
+      dst[i] = LatRec{r.frame, D.g.orig[r.arc], r.extra};
+    }
+    return;
+  }
   __shared__ unsigned long long s_pos;
   if (tid == 0) s_pos = 0;
   __syncthreads();
   for (long long i = tid; i < n_rec; i += NTH) {
-    const LatInt r = lat_ring[lat_first + i < lat_cap ? lat_first + i : lat_first + i - lat_cap];
+    const LatInt r = lat(i);
     const float v = __uint_as_float(te[foff[r.frame] + r.dst]) + r.extra;
     if (v <= D.lattice_beam) {
       const unsigned long long p = atomicAdd(&s_pos, 1ull);
