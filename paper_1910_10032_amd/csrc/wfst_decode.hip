@@ -25,7 +25,9 @@ static_assert(sizeof(TokOut) == sizeof(wfst_token_t), "token layout");
 static_assert(sizeof(Slot) == 16 && sizeof(HTok) == 16 && sizeof(Aux) == 16, "16-byte records");
 
 constexpr int NT = 512;          // threads of the workgroup that owns a lane
-constexpr int PARAM_RING = 8;    // pinned staging buffers for lane parameters
+constexpr int PARAM_RING = 8;    // pinned buffers for lane parameters
+constexpr size_t PINNED_WORDS_BYTES = (size_t)16 << 20;   // best-path words of a readout that go straight to pinned host memory
+constexpr int PATH_SNAP_W = 16;  // threads per channel of a best-path readout beside a running decode kernel
 
 struct wfst_graph {
   GraphDev dev{};
@@ -643,33 +645,47 @@ static int best_path_batch_impl(wfst_decoder_t *d, int64_t snap, const int32_t *
   rc = readout_stream(d, snap, &st);
   if (rc) return rc;
   const long long sn = snap > 0 ? (long long)snap : 0ll;
-  if (sizeof(int32_t) * (size_t)n * (size_t)std::max(words_cap, 1) > d->stage_bytes) {
-    HIP_TRY(hipStreamSynchronize(st));            // the staging buffer is about to be replaced
-    rc = ensure_stage(d, sizeof(int32_t) * (size_t)n * (size_t)std::max(words_cap, 1));
+  // Results that fit PINNED_WORDS_BYTES (a fixed place of words_cap words per channel) are written
+  // straight to the host; larger ones are packed in device memory and copied.
+  const size_t head = sizeof(PathOut) * (size_t)n, all_words = sizeof(int32_t) * (size_t)n * (size_t)std::max(words_cap, 1);
+  const bool direct = all_words <= PINNED_WORDS_BYTES;
+  if (head + (direct ? all_words : 0) > d->pin_bytes || (!direct && all_words > d->stage_bytes)) {
+    HIP_TRY(hipStreamSynchronize(st));            // a buffer is about to be replaced
+    rc = ensure_pinned(d, head + (direct ? all_words : 0));
+    if (!rc && !direct) rc = ensure_stage(d, all_words);
     if (rc) return rc;
   }
   rc = stage_channels(d, st, channels, n);
   if (rc) return rc;
-  HIP_TRY(hipMemsetAsync(d->d_cnt, 0, sizeof(unsigned long long), st));
-  if (snap > 0)      // beside a running decode kernel: one thread per channel
-    hipLaunchKernelGGL(k_best_path_words<1>, dim3((n + 63) / 64), dim3(64), 0, st, d->dev, (const int32_t *)d->d_chans, n,
-                       use_final, sn, (int32_t *)d->d_stage, words_cap, d->d_cnt, d->d_pathout);
+  PathOut *const d_po = (PathOut *)d->d_pin, *const po = (PathOut *)d->h_pin;
+  int32_t *const d_words = direct ? (int32_t *)((char *)d->d_pin + head) : (int32_t *)d->d_stage;
+  if (!direct) HIP_TRY(hipMemsetAsync(d->d_cnt, 0, sizeof(unsigned long long), st));
+  unsigned long long *const used_ctr = direct ? nullptr : d->d_cnt;
+  if (snap > 0)      // beside a running decode kernel: few waves
+    hipLaunchKernelGGL(k_best_path_words<PATH_SNAP_W>, dim3((n * PATH_SNAP_W + 63) / 64), dim3(64), 0, st, d->dev, (const int32_t *)d->d_chans, n,
+                       use_final, sn, d_words, words_cap, used_ctr, d_po);
   else
     hipLaunchKernelGGL(k_best_path_words<64>, dim3(n), dim3(64), 0, st, d->dev, (const int32_t *)d->d_chans, n,
-                       use_final, sn, (int32_t *)d->d_stage, words_cap, d->d_cnt, d->d_pathout);
+                       use_final, sn, d_words, words_cap, used_ctr, d_po);
   HIP_TRY(hipGetLastError());
-  std::vector<PathOut> po((size_t)n);
-  HIP_TRY(copy_sync_on(st, po.data(), d->d_pathout, sizeof(PathOut) * (size_t)n, hipMemcpyDeviceToHost));
-  long long used = 0;
-  for (int32_t i = 0; i < n; ++i) if (po[i].status == 0) used = std::max(used, po[i].word_off + po[i].n_words);
-  std::vector<int32_t> w((size_t)used);
-  if (used > 0) HIP_TRY(copy_sync_on(st, w.data(), d->d_stage, sizeof(int32_t) * (size_t)used, hipMemcpyDeviceToHost));
+  HIP_TRY(hipStreamSynchronize(st));
+  const int32_t *w = (const int32_t *)((const char *)d->h_pin + head);
+  std::vector<int32_t> copied;
+  if (!direct) {
+    long long used = 0;
+    for (int32_t i = 0; i < n; ++i) if (po[i].status == 0) used = std::max(used, po[i].word_off + po[i].n_words);
+    copied.resize((size_t)used);
+    if (used > 0) HIP_TRY(copy_sync_on(st, copied.data(), d->d_stage, sizeof(int32_t) * (size_t)used, hipMemcpyDeviceToHost));
+    w = copied.data();
+  }
   for (int32_t i = 0; i < n; ++i) {
     if (po[i].status == WFST_E_CAPACITY && po[i].n_words <= words_cap) {
       // the remembered-path scratch was too small for this path: trace it in full instead
       int32_t ch = channels[i];
       HIP_TRY(copy_sync_on(st, d->d_chans, &ch, sizeof(int32_t), hipMemcpyHostToDevice));
       d->staged_chans.clear();
+      rc = ensure_stage(d, sizeof(int32_t) * (size_t)std::max(words_cap, 1));
+      if (rc) return rc;
       hipLaunchKernelGGL(k_best_path, dim3(1), dim3(64), 0, st, d->dev, (const int32_t *)d->d_chans, use_final, sn,
                          (int32_t *)d->d_stage, words_cap, (uint32_t *)nullptr, 0, d->d_pathout);
       HIP_TRY(hipGetLastError());
@@ -678,7 +694,7 @@ static int best_path_batch_impl(wfst_decoder_t *d, int64_t snap, const int32_t *
         HIP_TRY(copy_sync_on(st, words + (size_t)i * words_cap, (int32_t *)d->d_stage + (words_cap - po[i].n_words),
                           sizeof(int32_t) * (size_t)po[i].n_words, hipMemcpyDeviceToHost));
     } else if (po[i].status == 0 && po[i].n_words > 0) {
-      std::memcpy(words + (size_t)i * words_cap, w.data() + po[i].word_off, sizeof(int32_t) * (size_t)po[i].n_words);
+      std::memcpy(words + (size_t)i * words_cap, w + po[i].word_off, sizeof(int32_t) * (size_t)po[i].n_words);
     }
     status[i] = po[i].status; n_words[i] = po[i].n_words; total_cost[i] = po[i].total_cost; reached_final[i] = po[i].reached_final;
   }

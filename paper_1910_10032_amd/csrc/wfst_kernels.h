@@ -311,15 +311,21 @@ __device__ __forceinline__ bool path_start(const DecDev &D, int ch, int use_fina
   const long long o = foff[F];
   const int n = (int)(foff[F + 1] - o);
   unsigned long long bf = ~0ull, bn = ~0ull; int bfi = -1, bni = -1;
-  for (int i = lane; i < n; i += W) {
-    const HTok t = hist[o + i];
-    const uint32_t h = t.handle & HMASK;
-    const unsigned long long kn = pack(okey(t.cost), h);
-    if (kn < bn) { bn = kn; bni = i; }
-    if (use_final) {
-      const float fc = __uint_as_float(rec[3 * (size_t)h + 2]);
-      if (fc != INFINITY) {
-        const unsigned long long kf = pack(okey(t.cost + fc), h);
+  constexpr int PU = 4;                        // tokens in flight (a lane past the end looks at the last one again)
+  for (int i0 = lane; i0 < n; i0 += W * PU) {
+    HTok t[PU]; float fc[PU];
+#pragma unroll
+    for (int u = 0; u < PU; ++u) t[u] = hist[o + min(i0 + u * W, n - 1)];
+#pragma unroll
+    for (int u = 0; u < PU; ++u) fc[u] = use_final ? __uint_as_float(rec[3 * (size_t)(t[u].handle & HMASK) + 2]) : INFINITY;
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      const uint32_t h = t[u].handle & HMASK;
+      const int i = min(i0 + u * W, n - 1);
+      const unsigned long long kn = pack(okey(t[u].cost), h);
+      if (kn < bn) { bn = kn; bni = i; }
+      if (fc[u] != INFINITY) {
+        const unsigned long long kf = pack(okey(t[u].cost + fc[u]), h);
         if (kf < bf) { bf = kf; bfi = i; }
       }
     }
@@ -372,20 +378,24 @@ __global__ void __launch_bounds__(64) k_best_path(DecDev D, const int32_t *chans
   out[blockIdx.x] = po;
 }
 
-// Best-path words of many channels (one wave each).  Back-pointers are unique, so two best
+// Best-path words of many channels, W threads each.  Back-pointers are unique, so two best
 // paths that share a token share everything before it: each channel remembers, per frame,
 // the token through which its last traced path entered the frame and the words up to there;
 // a new trace walks back only until it meets the remembered path (a chunk of frames plus the
 // distance to the merge point, not the whole utterance) and splices the remembered prefix.
-// Words of all channels are packed into `words` at po.word_off (allotted with one atomic add).
-// W = 64: one wave per channel (fastest when the GPU is otherwise idle).  W = 1: one thread
-// per channel, eight waves for 500 channels, which still find room beside a running decode
-// kernel whose workgroups hold nearly all wave slots.
+// The walk is a serial chain with one memory round trip per arc: where the frames start and what
+// the remembered path entered them through is fetched a frame ahead.  (Fetched when needed, they
+// made two more round trips per frame; 500 channels beside a decode kernel: 0.70 ms per readout.)
+// Words go to words + po.word_off: gi * words_cap, or, if words_used is given, packed (allotted
+// with one atomic add).
+// W = 64: one wave per channel (fastest when the GPU is otherwise idle).  W = 16: 125 waves for
+// 500 channels, which still find room on the compute units that hold a single lane of a running
+// decode kernel.
 template <int W>
 __global__ void __launch_bounds__(64) k_best_path_words(DecDev D, const int32_t *chans, int n_ch, int use_final, long long snap_id,
                                                         int32_t *words, int words_cap, unsigned long long *words_used, PathOut *out) {
   const int gi = (int)((blockIdx.x * blockDim.x + threadIdx.x) / W);      // channel of this thread group
-  if (gi >= n_ch) return;                                                // (W = 64: one group per block)
+  if (gi >= n_ch) return;
   const int ch = chans[gi];
   const int lane = threadIdx.x % W;
   ChanState *cs = D.chan + ch;
@@ -394,8 +404,7 @@ __global__ void __launch_bounds__(64) k_best_path_words(DecDev D, const int32_t 
   int32_t *entry = D.pc_entry + (size_t)ch * (size_t)(D.max_frames + 2);
   int32_t *wcount = D.pc_wcount + (size_t)ch * (size_t)(D.max_frames + 2);
   int32_t *cw = D.pc_words + (size_t)ch * (size_t)D.pc_wcap;
-  __shared__ int sh[4];                      // status, total words, merge frame, new words (W > 1)
-  __shared__ long long sh_off;
+  auto from_first = [&](int v) { return __shfl(v, (int)(threadIdx.x & 63) & ~(W - 1), 64); };   // of this group's lanes
   PathOut po{0, 0, 0, 0, 0.f, 0, 0};
   int F = 0, cur = 0;
   const ChanView cv = chan_view(D, ch, snap_id);
@@ -406,38 +415,41 @@ __global__ void __launch_bounds__(64) k_best_path_words(DecDev D, const int32_t 
     const int cached_nf = cs->path_nf;
     int f = F, base = 0;
     const long long max_steps = cv.hist_used + 1;
-    // the token of the next step is fetched while this step's word label is still on its way
-    auto in_frame = [&](int ff, int c) { return ff >= 0 && c >= 0 && (long long)c < foff[ff + 1] - foff[ff]; };
+    // start of frame f and of the next one, and, on their way, those of the frames before; the
+    // remembered path's token in frame f, and in the frame before
+    long long o = foff[f], o_end = foff[f + 1], o1 = f >= 1 ? foff[f - 1] : 0, o2 = f >= 2 ? foff[f - 2] : 0;
+    auto remembered = [&](int ff) { return ff >= 0 && ff < cached_nf ? entry[ff] : -1; };
+    int e0 = remembered(f), e1 = remembered(f - 1);
     HTok t{};
-    if (!in_frame(f, cur)) status = E_BROKEN_TRACE; else t = hist[foff[f] + cur];
+    if (cur < 0 || (long long)cur >= o_end - o) status = E_BROKEN_TRACE; else t = hist[o + cur];
     for (long long step = 0; status == 0; ++step) {
       if (t.in_arc == NO_ARC) break;
       if (t.prev == NO_ARC || step > max_steps) { status = E_BROKEN_TRACE; break; }
       const bool is_entry = !(t.prev & PREV_SAME);
       if (is_entry) {
-        if (f < cached_nf && entry[f] == cur) { base = wcount[f]; merge_f = f; break; }
+        if (e0 >= 0 && e0 == cur) { base = wcount[f]; merge_f = f; break; }
         entry[f] = cur; wcount[f] = k;        // k: words found so far, all later on the path; fixed up below
+        --f; o_end = o; o = o1; o1 = o2; o2 = f >= 2 ? foff[f - 2] : 0;
+        e0 = e1; e1 = remembered(f - 1);
       }
-      const int32_t w = D.g.label[t.in_arc];
-      const int ncur = is_entry ? (int)t.prev : (int)(t.prev & ~PREV_SAME);
-      const int nf = is_entry ? f - 1 : f;
-      HTok tn{};
-      const bool ok2 = in_frame(nf, ncur);
-      if (ok2) tn = hist[foff[nf] + ncur];
+      // the next token and this arc's word are fetched together
+      cur = (int)(t.prev & ~PREV_SAME);
+      const uint32_t arc = t.in_arc;
+      const bool ok2 = f >= 0 && (long long)cur < o_end - o;
+      if (ok2) t = hist[o + cur];
+      const int32_t w = D.g.label[arc];
       if (w != 0) {
         if (k < D.pc_wcap) cw[D.pc_wcap - 1 - k] = w;
         ++k;
       }
-      if (!ok2) { status = E_BROKEN_TRACE; break; }
-      cur = ncur; f = nf; t = tn;
+      if (!ok2) status = E_BROKEN_TRACE;
     }
     if (status == 0 && (long long)base + 2ll * k > (long long)D.pc_wcap) status = E_CAPACITY;
     total = base + k;
   }
   if constexpr (W > 1) {
-    if (lane == 0) { sh[0] = status; sh[1] = total; sh[2] = merge_f; sh[3] = k; }
-    __syncthreads();
-    status = sh[0]; total = sh[1]; merge_f = sh[2]; k = sh[3];
+    status = from_first(status); total = from_first(total); merge_f = from_first(merge_f); k = from_first(k);
+    __threadfence_block();                     // (the first lane's stores, before the others read them)
   }
   if (status != 0) {
     if (lane == 0) { cs->path_nf = 0; po.status = status; po.n_words = total; out[gi] = po; }
@@ -446,20 +458,19 @@ __global__ void __launch_bounds__(64) k_best_path_words(DecDev D, const int32_t 
   for (int f = merge_f + 1 + lane; f <= F; f += W) wcount[f] = total - wcount[f];
   const int base = total - k;
   for (int j = lane; j < k; j += W) cw[base + j] = cw[D.pc_wcap - k + j];
-  if constexpr (W > 1) __syncthreads();
-  long long off = 0;
+  if constexpr (W > 1) __threadfence_block();
+  long long off = (long long)gi * words_cap;
   if (lane == 0) {
     cs->path_nf = F + 1;
     po.n_words = total;
     if (total > words_cap) po.status = E_CAPACITY;
-    else po.word_off = (long long)atomicAdd(words_used, (unsigned long long)total);
-    off = po.word_off;
+    else if (words_used) off = (long long)atomicAdd(words_used, (unsigned long long)total);
+    po.word_off = off;
     out[gi] = po;
   }
   if constexpr (W > 1) {
-    if (lane == 0) { sh[0] = po.status; sh_off = off; }
-    __syncthreads();
-    po.status = sh[0]; off = sh_off;
+    po.status = from_first(po.status);
+    off = (long long)(((unsigned long long)(uint32_t)from_first((int)(off >> 32)) << 32) | (uint32_t)from_first((int)off));
   }
   if (po.status != 0) return;
   for (int j = lane; j < total; j += W) words[off + j] = cw[j];
