@@ -198,18 +198,29 @@ class WfstDecoder:
         (device_ptr, stride) pairs together with n_frames.  With snapshot_every > 0 the lanes seal
         a snapshot after every that many frames; returns (first snapshot id, number of snapshots)."""
         ch = np.ascontiguousarray(channels, np.int32)
-        n = len(ch)
-        ptrs = np.empty(n, np.uint64)
-        strides = np.empty(n, np.int32)
-        nfr = np.empty(n, np.int32)
-        for i, t in enumerate(loglikes):
-            if isinstance(t, tuple):
-                ptrs[i], strides[i] = t
-                nfr[i] = n_frames[i]
-            else:
-                assert t.is_cuda and t.dim() == 2 and t.stride(1) == 1 and str(t.dtype) == "torch.float32"
-                ptrs[i], strides[i] = t.data_ptr(), t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1])
-                nfr[i] = t.shape[0] if n_frames is None else n_frames[i]
+        assert len(loglikes) == len(ch)
+        if len(ch) and not any([isinstance(t, tuple) for t in loglikes]):
+            import torch
+            f32 = torch.float32
+            # (one attribute at a time over the whole list: this runs once per lane and call)
+            shapes, pitches = [t.shape for t in loglikes], [t.stride() for t in loglikes]
+            assert all([len(p) == 2 and p[1] == 1 for p in pitches]) and all([t.is_cuda and t.dtype is f32 for t in loglikes])
+            ptrs = np.array([t.data_ptr() for t in loglikes], np.uint64)
+            strides = np.array([p[0] if s[0] > 1 else max(p[0], s[1]) for s, p in zip(shapes, pitches)], np.int32)
+            nfr = np.array([s[0] for s in shapes] if n_frames is None else n_frames[:len(shapes)], np.int32)
+        else:
+            n = len(ch)
+            ptrs = np.empty(n, np.uint64)
+            strides = np.empty(n, np.int32)
+            nfr = np.empty(n, np.int32)
+            for i, t in enumerate(loglikes):
+                if isinstance(t, tuple):
+                    ptrs[i], strides[i] = t
+                    nfr[i] = n_frames[i]
+                else:
+                    assert t.is_cuda and t.dim() == 2 and t.stride(1) == 1 and str(t.dtype) == "torch.float32"
+                    ptrs[i], strides[i] = t.data_ptr(), t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1])
+                    nfr[i] = t.shape[0] if n_frames is None else n_frames[i]
         if stream is None:
             import torch
             stream = torch.cuda.current_stream().cuda_stream
