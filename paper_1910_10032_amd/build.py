@@ -6,7 +6,7 @@ _DIR = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(_DIR, "_libwfst_decode.so")
 SOURCES = [os.path.join(_DIR, "csrc", "wfst_decode.hip")]
 HEADERS = [os.path.join(_DIR, "csrc", h) for h in ("wfst_device.h", "wfst_lane.h", "wfst_frame_general.h",
-                                                    "wfst_frame_light.h", "wfst_kernels.h")] + [
+                                                    "wfst_frame_heavy.h", "wfst_frame_light.h", "wfst_kernels.h")] + [
     os.path.join(os.path.dirname(_DIR), "include", "wfst_decode.h")]
 
 

@@ -25,6 +25,7 @@ static_assert(sizeof(TokOut) == sizeof(wfst_token_t), "token layout");
 static_assert(sizeof(Slot) == 16 && sizeof(HTok) == 16 && sizeof(Aux) == 16, "16-byte records");
 
 constexpr int NT = 512;          // threads of the workgroup that owns a lane
+constexpr int NUM_XCDS = 8;      // the dispatcher deals workgroups to them in turn
 constexpr int PARAM_RING = 8;    // pinned buffers for lane parameters
 constexpr size_t PINNED_WORDS_BYTES = (size_t)16 << 20;   // best-path words of a readout that go straight to pinned host memory
 constexpr int PATH_SNAP_W = 16;  // threads per channel of a best-path readout beside a running decode kernel
@@ -41,13 +42,15 @@ struct wfst_decoder {
   const wfst_graph *graph = nullptr;
   wfst_config_t cfg{};
   DecDev dev{};
+  DecDev *d_dev = nullptr;              // a copy in device memory
   int64_t per_channel_bytes = 0, per_lane_bytes = 0, total_bytes = 0;
   std::vector<void *> allocs;
   std::vector<uint8_t> inited;          // host mirror: channel has been initialised
   std::vector<int64_t> frames_fed;      // host mirror: rows of scores handed to the channel
   std::vector<uint32_t> stamp;          // duplicate detection within a call
   uint32_t stamp_now = 0;
-  WideLane *d_wide = nullptr;           // [max_lanes] lanes shared by several workgroups (lane_workgroups > 1)
+  int team_lanes = 0;                   // how many lanes can have several workgroups
+  uint32_t launches = 0;                // of kernels with teams, so far
   void *h_pinned = nullptr;             // pinned: lane parameters and progress words
   LaneParam *h_params[PARAM_RING] = {}, *d_params[PARAM_RING] = {};   // pinned [max_lanes], and its device address
   hipEvent_t param_ev[PARAM_RING] = {};
@@ -150,10 +153,21 @@ int check_channels(wfst_decoder *d, const int32_t *channels, int32_t n, bool nee
   return 0;
 }
 
-// Put the lane parameters into a pinned ring and launch the lane kernel.  wide: several
-// workgroups per lane (only for calls without snapshots whose lanes x workgroups fit the device
-// at one workgroup per compute unit, so that all of them are resident and can wait for each other).
-int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init, hipStream_t stream, bool wide = false) {
+// How many workgroups a lane gets when a call has n lanes: as many as the device has compute units
+// for, on one XCD with each other (lane i of a call runs on XCD i % 8), but no more than TEAM_MAX and
+// no more than the configuration allows (0: the library's choice).  They help with heavy frames
+// only; a lane that has had none for a while sends them away.
+int lane_team(const wfst_decoder *d, int n) {
+  const wfst_config_t &c = d->cfg;
+  const int per_xcd = d->num_cus / NUM_XCDS, lanes_per_xcd = (n + NUM_XCDS - 1) / NUM_XCDS;
+  const int most = c.lane_workgroups == 0 ? TEAM_MAX : std::min(c.lane_workgroups, TEAM_MAX);
+  if (c.lane_workgroups <= 1 && (c.lane_workgroups == 1 || (c.lane_threads != 0 && c.lane_threads != 1024))) return 1;
+  if (c.frame_form != 0 || n > d->team_lanes) return 1;
+  return std::max(1, std::min(most, per_xcd / lanes_per_xcd));
+}
+
+// Put the lane parameters into a pinned ring and launch the lane kernel.
+int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init, hipStream_t stream) {
   const int n = (int)lp.size();
   if (n == 0) return 0;
   const int slot = d->ring_pos;
@@ -166,26 +180,20 @@ int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init,
     HIP_TRY(hipEventCreate(&e0)); HIP_TRY(hipEventCreate(&e1));
     HIP_TRY(hipEventRecord(e0, stream));
   }
-  // A lane is one workgroup.  With at most one lane per compute unit a lane can have the whole
-  // unit: 1024 threads; with more lanes two 512-thread workgroups share a unit.  The results
-  // do not depend on the choice.
-  if (wide) {
-    const int G = std::min(d->cfg.lane_workgroups, d->num_cus / n);
-    hipLaunchKernelGGL(k_zero_wide, dim3((n + 63) / 64), dim3(64), 0, stream, d->d_wide, n);
-    hipLaunchKernelGGL(k_advance_wide<1024>, dim3(n * G), dim3(1024), 0, stream, d->dev, params, d->d_wide, G);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipEventRecord(d->param_ev[slot], stream));
-    if (e0) { HIP_TRY(hipEventRecord(e1, stream)); d->prof_events.push_back({e0, e1}); }
-    return 0;
-  }
+  // With at most one lane per compute unit a lane can have the whole unit: 1024 threads; with more
+  // lanes two 512-thread workgroups share a unit.  The results do not depend on the choice.
   int threads = d->cfg.lane_threads;
   if (threads == 0) threads = n <= d->num_cus ? 1024 : NT;
-  if (threads == 1024)
-    hipLaunchKernelGGL(k_advance<1024>, dim3(n), dim3(1024), 0, stream, d->dev, params, is_init);
+  const int team = is_init ? 1 : lane_team(d, n);
+  if (team > 1) {
+    const int n8 = (n + NUM_XCDS - 1) / NUM_XCDS * NUM_XCDS;
+    hipLaunchKernelGGL((k_advance<1024, true>), dim3(n8 * team), dim3(1024), 0, stream, d->dev, (const DecDev *)d->d_dev, params, 0, n, n8, ++d->launches);
+  } else if (threads == 1024)
+    hipLaunchKernelGGL((k_advance<1024, false>), dim3(n), dim3(1024), 0, stream, d->dev, (const DecDev *)d->d_dev, params, is_init, n, n, 0u);
   else if (threads == 256)
-    hipLaunchKernelGGL(k_advance<256>, dim3(n), dim3(256), 0, stream, d->dev, params, is_init);
+    hipLaunchKernelGGL((k_advance<256, false>), dim3(n), dim3(256), 0, stream, d->dev, (const DecDev *)d->d_dev, params, is_init, n, n, 0u);
   else
-    hipLaunchKernelGGL(k_advance<NT>, dim3(n), dim3(NT), 0, stream, d->dev, params, is_init);
+    hipLaunchKernelGGL((k_advance<NT, false>), dim3(n), dim3(NT), 0, stream, d->dev, (const DecDev *)d->d_dev, params, is_init, n, n, 0u);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(d->param_ev[slot], stream));
   if (e0) { HIP_TRY(hipEventRecord(e1, stream)); d->prof_events.push_back({e0, e1}); }
@@ -383,10 +391,10 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
   D.lattice_on = c.lattice_on ? 1 : 0; D.beam = c.beam; D.lattice_beam = c.lattice_beam;
   D.force_general = c.frame_form == 1 ? 1 : 0;
   D.approximate = c.approximate;
-  D.wide_spin_limit = WIDE_SPIN_LIMIT;
+  D.team_spin_limit = TEAM_SPIN_LIMIT;
   if (const char *e = std::getenv("WFST_DECODE_WIDE_SPIN_LIMIT")) {   // a testing aid: give lane barriers up early
     const long v = std::strtol(e, nullptr, 10);
-    if (v >= 1 && v <= (long)WIDE_SPIN_LIMIT) D.wide_spin_limit = (uint32_t)v;
+    if (v >= 1 && v <= (long)TEAM_SPIN_LIMIT) D.team_spin_limit = (uint32_t)v;
   }
   D.hist_cap = c.history_capacity; D.lat_cap = c.lattice_on ? c.lattice_capacity : 1;
   const size_t nc = (size_t)c.num_channels, nl = (size_t)c.max_lanes;
@@ -407,7 +415,11 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
   if (!rc) rc = dev_alloc(d, &D.aux, nl * (size_t)D.auxcap);
   if (!rc) rc = dev_alloc(d, &D.dkey, nl * (size_t)D.tokcap);
   if (!rc) rc = dev_alloc(d, &D.dslot, nl * (size_t)D.tokcap);
-  if (!rc && c.lane_workgroups > 1) rc = dev_alloc(d, &d->d_wide, nl);
+  d->team_lanes = c.lane_workgroups == 1 || c.frame_form != 0 ? 0 : (int)std::min<int64_t>((int64_t)nl, d->num_cus / 2);
+  if (!rc && d->team_lanes > 0) {
+    rc = dev_alloc(d, &D.teams, (size_t)d->team_lanes);
+    if (!rc && hipMemset(D.teams, 0, sizeof(TeamLane) * (size_t)d->team_lanes) != hipSuccess) rc = WFST_E_DEVICE;
+  }
   d->per_lane_bytes = (d->total_bytes - before_lanes) / (int64_t)nl;
   if (!rc) rc = dev_alloc(d, &d->d_chans, std::max(nc, nl));
   if (!rc) rc = dev_alloc(d, &d->d_pathout, std::max(nc, nl));
@@ -451,6 +463,7 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
       D.lane_sealed = (long long *)((char *)pinned_dev + ring_bytes);
       std::memset(d->h_sealed, 0, sizeof(long long) * nl);
     }
+    ok = ok && hipMalloc((void **)&d->d_dev, sizeof(DecDev)) == hipSuccess && hipMemcpy(d->d_dev, &D, sizeof(DecDev), hipMemcpyHostToDevice) == hipSuccess;
     if (ok) {
       hipLaunchKernelGGL(k_fill_slots, dim3(1024), dim3(256), 0, 0, D.slots, nl * (size_t)D.H);
       ok = hipGetLastError() == hipSuccess && hipDeviceSynchronize() == hipSuccess;
@@ -467,6 +480,7 @@ void wfst_decode_destroy(wfst_decoder_t *d) {
   if (!d) return;
   (void)hipDeviceSynchronize();
   for (void *p : d->allocs) (void)hipFree(p);
+  if (d->d_dev) (void)hipFree(d->d_dev);
   if (d->d_stage) (void)hipFree(d->d_stage);
   if (d->h_pin) (void)hipHostFree(d->h_pin);
   for (int i = 0; i < PARAM_RING; ++i) {
@@ -557,8 +571,7 @@ static int advance_impl(wfst_decoder_t *d, const int32_t *channels, int32_t n_la
     HIP_TRY(hipGetLastError());
     for (int32_t j = 0; j < n_snaps; ++j) d->blk_ids[(size_t)((id0 + j) % d->dev.n_blk)] = id0 + j;
   }
-  const bool wide = d->cfg.lane_workgroups > 1 && n_snaps == 0 && 2 * n_lanes <= d->num_cus;
-  rc = launch_lanes(d, lp, 0, (hipStream_t)stream, wide);
+  rc = launch_lanes(d, lp, 0, (hipStream_t)stream);
   if (rc) return rc;
   HIP_TRY(hipEventRecord(d->last_advance, (hipStream_t)stream));
   d->have_last_advance = true;

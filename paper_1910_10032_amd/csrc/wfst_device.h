@@ -97,6 +97,7 @@ struct ChanState {
   long long arcs_expanded;
   int32_t max_pre, max_post, closure_iters_max;
   int32_t path_nf;           // frames covered by the remembered best path (0 = none)
+  int32_t last_heavy, pad;   // the last frame that was not a light one
 };
 
 // The state of a channel sealed at a frame boundary, for readouts that run while later
@@ -121,6 +122,7 @@ struct LaneParam {
   int32_t n_snaps, pad;      // snapshots the lane seals in this call (the last ones at its end state)
 };
 
+struct TeamLane;
 struct DecDev {
   GraphDev g;
   ChanState *chan;
@@ -138,6 +140,7 @@ struct DecDev {
   Aux *aux;                  // [max_lanes][auxcap]
   uint32_t *dkey;            // [max_lanes][tokcap] dense cost keys for the selection
   uint32_t *dslot;           // [max_lanes][tokcap]
+  TeamLane *teams;           // lanes with several workgroups
   int32_t *pc_entry;         // [num_channels][max_frames + 2] remembered best path: token through
                              // which it entered each frame
   int32_t *pc_wcount;        // [num_channels][max_frames + 2] its words up to (and with) that arc
@@ -149,10 +152,14 @@ struct DecDev {
   float beam, lattice_beam;
   int32_t force_general;         // 1: every frame takes the general form
   int32_t approximate;           // 1: max-active by a single histogram cut (not exact)
-  uint32_t wide_spin_limit;      // polls before a lane barrier is given up (lanes shared by several workgroups)
+  uint32_t team_spin_limit;      // polls before a barrier of a lane's workgroups is given up
   int32_t pad3;
   unsigned long long *dbg;   // phase timers of instrumented builds, else null
 };
+
+// The decoder's description where it does not change and every thread reads the same: in device
+// memory, read through the scalar cache (functions that are called and not inlined get it this way).
+typedef const __attribute__((address_space(4))) DecDev ConstDev;
 
 // error codes mirrored from the public header (device code cannot include it cleanly)
 constexpr int E_TOKEN_OVERFLOW = -6, E_LATTICE_OVERFLOW = -7, E_DEAD_CHANNEL = -8, E_NAN_INPUT = -9,

@@ -4,123 +4,25 @@
 
 namespace wfst {
 
-// Several workgroups on one lane (Section 3.1: a batch too small to fill the device is bound by
-// latency; Section 3.3: the persistent kernel): workgroup g of the lane's G takes every G-th
-// tile of tokens, window of queue entries and block of notes; the frame's counters and the
-// selection's histogram live in global memory (WideLane), and where one workgroup would pass a
-// workgroup barrier the lane's workgroups meet at a lane barrier: each makes its stores visible
-// device-wide, counts itself in, and waits (a bounded number of polls) until all have.
-struct WideCtx {
-  int g, G;                    // this workgroup's number among the lane's, and how many there are
-  WideLane *wl;
-  unsigned long long epoch;    // arrivals expected at the next barrier (thread 0 keeps count)
-  unsigned spin_limit;
-};
-constexpr unsigned WIDE_SPIN_LIMIT = 1u << 22;      // default number of polls before a barrier is given up (seconds)
-
-// Returns false (to every thread of the workgroup) if a barrier of the lane was given up: the
-// workgroup must then stop working on the lane (what it would read may be incomplete).
-template <int NT>
-__device__ __forceinline__ bool lane_sync(WideCtx &W, LaneShared<NT> &S) {
-  __syncthreads();                                  // every wave's stores have been acknowledged
-  if (threadIdx.x == 0) {
-    W.epoch += (unsigned long long)W.G;
-    bool ok = !ld32(&W.wl->broken);
-    if (ok) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      atomicAdd(&W.wl->arrived, 1ull);
-      unsigned spins = 0;
-      while (ld64(&W.wl->arrived) < W.epoch) {
-        if (++spins > W.spin_limit || ld32(&W.wl->broken)) { atomicExch(&W.wl->broken, 1u); ok = false; break; }
-        __builtin_amdgcn_s_sleep(4);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
-    S.wide_ok = ok ? 1u : 0u;
-  }
-  __syncthreads();
-  return S.wide_ok != 0;
-}
-
-// The exact selection by all workgroups of a lane together (see block_select); every workgroup
-// arrives at the same result.  Each workgroup counts its share in LDS and adds the bins it
-// filled to the pass's histogram in global memory.  Passes rotate through three histograms, so
-// that one lane barrier per pass is enough: pass p counts into histogram p % 3 (zero since pass
-// p - 1 at the latest), the barrier, then every workgroup reads it and zeroes histogram
-// (p + 2) % 3, which nobody reads any more (its readers passed the barrier of pass p) and nobody
-// counts into before the barrier of pass p + 1.  `pass` is the lane's running pass number (the
-// same in all workgroups); histograms 0 and 1 are zero at the start of a frame.
-template <int NT, class F>
-__device__ bool wide_select(LaneShared<NT> &S, WideCtx &W, uint32_t &pass, int n, uint32_t need, uint32_t lo, uint32_t hi, F val,
-                            uint32_t &theta, uint32_t &n_less, uint32_t &n_eq, bool one_pass) {
-  const int tid = threadIdx.x;
-  constexpr int PER = NBINS / NT;
-  const uint32_t gtid = (uint32_t)W.g * NT + tid, gstr = (uint32_t)W.G * NT;
-  uint32_t less = 0;
-  for (;;) {
-    int shift = 0;
-    while ((((unsigned long long)hi - lo) >> shift) >= (unsigned long long)NBINS) ++shift;
-    uint32_t *hist = W.wl->hist[pass % 3], *hist_next = W.wl->hist[(pass + 2) % 3];
-    ++pass;
-    for (int b = tid; b < NBINS; b += NT) S.hist[b] = 0;
-    __syncthreads();
-    for (uint32_t i = gtid; i < (uint32_t)n; i += gstr) {
-      uint32_t v;
-      if (val((int)i, v) && v >= lo && v <= hi) atomicAdd(&S.hist[(v - lo) >> shift], 1u);
-    }
-    __syncthreads();
-    for (int b = tid; b < NBINS; b += NT) { const uint32_t cnt = S.hist[b]; if (cnt) atomicAdd(&hist[b], cnt); }
-    if (!lane_sync<NT>(W, S)) return false;
-    uint32_t loc[PER], sum = 0;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) { loc[q] = ld32(&hist[tid * PER + q]); sum += loc[q]; }
-    for (uint32_t b = gtid; b < (uint32_t)NBINS; b += gstr) hist_next[b] = 0;
-    int total;
-    uint32_t run = (uint32_t)block_excl_scan<NT>((int)sum, S.wave_tmp, total);
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      if (run < need && run + loc[q] >= need) { S.sel_bin = tid * PER + q; S.sel_below = run; S.sel_cnt = loc[q]; }
-      run += loc[q];
-    }
-    __syncthreads();
-    const uint32_t b = S.sel_bin, below = S.sel_below, cnt = S.sel_cnt;
-    __syncthreads();
-    if (one_pass) {                                 // the approximate cut: the bin's upper edge
-      const unsigned long long edge = (unsigned long long)lo + ((unsigned long long)(b + 1) << shift) - 1ull;
-      theta = edge < hi ? (uint32_t)edge : hi; n_less = 0; n_eq = 0;
-      return true;
-    }
-    less += below;
-    need -= below;
-    lo = lo + (b << shift);
-    unsigned long long nhi = (unsigned long long)lo + ((1ull << shift) - 1);
-    if (nhi < hi) hi = (uint32_t)nhi;
-    if (shift == 0) { theta = lo; n_less = less; n_eq = cnt; return true; }
-  }
-}
-
 // One frame of one lane in its general form: state table, token queue and candidate notes in
 // the lane's global scratch, tokens and state headers read from memory.  It handles frames of
-// any size (up to the decoder's capacities) and every graph; light frames take the LDS form
-// in wfst_frame_light.h instead.  Stages as listed at the top of wfst_kernels.h.  WIDE: the
-// lane is shared by W.G workgroups (each with its own replica of the lane's state in S).
-template <int NT, bool WIDE>
-__device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, const float *ll, bool is_init,
-                           Slot *gslots, uint32_t *queue, Aux *aux, uint32_t *dkey, uint32_t *dslot,
-                           long long *foff, HTok *hist, LatInt *lat) {
+// any size (up to the decoder's capacities) and every graph; what fits the LDS forms takes those
+// (wfst_frame_light.h, wfst_frame_heavy.h).  Stages as listed at the top of wfst_kernels.h.
+// (A function of its own, as the heavy frame.)
+template <int NT, bool TEAM>
+__device__ __attribute__((noinline)) void general_frame(ConstDev *Dp, int my_lane, int chan, const float *ll, int is_init) {
+  ConstDev &D = *(ConstDev *)uni((unsigned long long)Dp);
+  LaneShared<NT> &S = lane_lds<NT, TEAM>();
+  my_lane = uni(my_lane); chan = uni(chan); ll = (const float *)uni((unsigned long long)ll); is_init = uni(is_init);
+  Slot *const gslots = D.slots + (size_t)my_lane * D.H;
+  uint32_t *const queue = D.queue + (size_t)my_lane * (size_t)D.qcap;
+  Aux *const aux = D.aux + (size_t)my_lane * (size_t)D.auxcap;
+  uint32_t *const dkey = D.dkey + (size_t)my_lane * (size_t)D.tokcap, *const dslot = D.dslot + (size_t)my_lane * (size_t)D.tokcap;
+  long long *const foff = D.frame_off + (size_t)chan * (size_t)(D.max_frames + 2);
+  HTok *const hist = D.hist + (size_t)chan * (size_t)D.hist_cap;
+  LatInt *const lat = D.lat + (size_t)chan * (size_t)D.lat_cap;
   const int tid = threadIdx.x;
-  GenCtr *Cp;
-  if constexpr (WIDE) Cp = &W.wl->c; else Cp = &S.gen;
-  GenCtr &C = *Cp;
-  // counters are read through these: plain in LDS, past the vector cache in global memory
-  auto R32 = [&](const uint32_t *p) -> uint32_t { if constexpr (WIDE) return ld32(p); else return *p; };
-  auto R64 = [&](const unsigned long long *p) -> unsigned long long { if constexpr (WIDE) return ld64(p); else return *p; };
-  // the lane's barrier; a workgroup leaves the frame (and the lane) if the barrier was given up
-#define LSYNC() do { if constexpr (WIDE) { if (!lane_sync<NT>(W, S)) { if (threadIdx.x == 0) S.status = E_DEVICE; __syncthreads(); return; } } \
-                     else __syncthreads(); } while (0)
-  const uint32_t wg = WIDE ? (uint32_t)W.g : 0u, nwg = WIDE ? (uint32_t)W.G : 1u;
-  const uint32_t gtid = wg * NT + (uint32_t)tid, gstr = nwg * NT;
-  const bool lead = wg == 0 && tid == 0;            // the one thread of the lane that writes what exists once
+  GenCtr &C = S.gen;
   const uint32_t *rec = D.g.rec;
   constexpr bool LDS = false;                // table words are read with coherent global loads
 #ifdef WFST_PHASE_TIMING
@@ -131,15 +33,11 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
   const int hbits = D.hbits;
   const Slot fresh{~0ull, EMPTY, A_FRESH};
 
-  if constexpr (WIDE) {                             // the first two histograms of the selection start at zero
-    for (uint32_t b = gtid; b < 2u * NBINS; b += gstr) W.wl->hist[b / NBINS][b % NBINS] = 0;
-  }
-  uint32_t sel_pass = 0;
-  if (lead) {
+  if (tid == 0) {
     C.claim_ctr = 0; C.auxn = 0; C.best = KEY_NONE; C.flags = 0; C.nvalid = 0; C.nout = 0; C.latn = 0;
     C.kmin = 0xFFFFFFFFu; C.kmax = 0; C.emit_arcs = 0; C.eps_arcs = 0;
   }
-  LSYNC();
+  __syncthreads();
   const int nf = S.nf;                       // index of the frame being written
   const long long out_base = S.hist_used;
   int abort_code = 0;
@@ -196,16 +94,15 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
         }
       };
       uint32_t h, hn = 0; float c, cn = 0.f; int ne, nen = 0;
-      const int tb0 = (int)(wg * NT), tstep = (int)gstr;     // this workgroup's tiles
-      load_token(tb0 + tid, h, c, ne);
-      for (int tb = tb0; tb < n_in; tb += tstep) {
+      load_token(tid, h, c, ne);
+      for (int tb = 0; tb < n_in; tb += NT) {
         int total;
         const int ex = block_excl_scan<NT, LDS>(ne, S.wave_tmp, total);
         S.scan[tid] = ex; S.cost[tid] = c; S.base[tid] = h + 1;
         wg_sync<LDS>();
         GEN_MARK(8);
-        if (tid == 0 && total) { if constexpr (WIDE) atomicAdd(&C.emit_arcs, (unsigned long long)total); else C.emit_arcs += (unsigned long long)total; }
-        if (tb + tstep < n_in) load_token(tb + tstep + tid, hn, cn, nen);   // next tile, in flight during this one's rounds
+        if (tid == 0) C.emit_arcs += (unsigned long long)total;
+        if (tb + NT < n_in) load_token(tb + NT + tid, hn, cn, nen);   // next tile, in flight during this one's rounds
         // one thread per arc (Section 3.3), EXP_U arcs of the tile per thread and round so
         // that their loads are in flight together
         for (int j0 = 0; j0 < total; j0 += NT * EXP_U) {
@@ -255,7 +152,7 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
           if ((tid & 63) == 0 && m != KEY_NONE) atomicMin(&C.best, m);
           wg_sync<LDS>();
           GEN_MARK(9);
-          const float cut = key2f(R32(&C.best)) + D.beam;     // running bound, never below the final cutoff
+          const float cut = key2f(C.best) + D.beam;     // running bound, never below the final cutoff
 #pragma unroll
           for (int u = 0; u < EXP_U; ++u) {
             if (kx[u] == KEY_NONE || !(x[u] <= cut)) continue;
@@ -277,11 +174,11 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
       asm volatile("" ::"v"(touch), "v"(touch_more));
     }
   }
-  LSYNC();
+  __syncthreads();
   GEN_MARK(0);
-  const uint32_t bestk = R32(&C.best);
+  const uint32_t bestk = C.best;
   if (abort_code == 0) {
-    const uint32_t fl = R32(&C.flags);
+    const uint32_t fl = C.flags;
     if (fl & F_NAN) abort_code = E_NAN_INPUT;
     else if (fl & F_TOKOVF) abort_code = E_TOKEN_OVERFLOW;
     else if (fl & F_LATOVF) abort_code = E_LATTICE_OVERFLOW;
@@ -303,18 +200,18 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
   };
   int iters = 0;
   if (abort_code == 0) {
-    uint32_t w0 = 0, w1 = min((uint32_t)R64(&C.claim_ctr), qcap);
-    LSYNC();
+    uint32_t w0 = 0, w1 = min((uint32_t)C.claim_ctr, qcap);
+    __syncthreads();
     while (w0 < w1) {
       // every thread takes CU queue entries of the window per pass, their loads side by side; the
       // pass is kept convergent (predicated, no early exit) so that the wave can allot note space
       // with one atomic
       constexpr int CU = 4;
-      for (uint32_t i0 = w0; i0 < w1; i0 += gstr * CU) {
+      for (uint32_t i0 = w0; i0 < w1; i0 += NT * CU) {
         bool act[CU], first[CU]; uint32_t src[CU], h[CU], ne[CU], np[CU]; float c[CU]; Slot sv[CU];
 #pragma unroll
         for (int u = 0; u < CU; ++u) {
-          const uint32_t i = i0 + (uint32_t)u * gstr + gtid;
+          const uint32_t i = i0 + (uint32_t)u * NT + tid;
           act[u] = false; first[u] = false; src[u] = 0; h[u] = 0; ne[u] = 0; np[u] = 0; c[u] = 0.f;
           if (i < w1) {
             bool eps, dup;
@@ -370,18 +267,18 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
           if (first[u]) note += np[u];
         }
       }
-      LSYNC();
+      __syncthreads();
       GEN_MARK(11);
-      w0 = w1; w1 = min((uint32_t)R64(&C.claim_ctr), qcap);
+      w0 = w1; w1 = min((uint32_t)C.claim_ctr, qcap);
       ++iters;
-      LSYNC();
+      __syncthreads();
     }
-    const uint32_t fl2 = R32(&C.flags);
+    const uint32_t fl2 = C.flags;
     if (fl2 & F_TOKOVF) abort_code = E_TOKEN_OVERFLOW;
     else if (fl2 & F_LATOVF) abort_code = E_LATTICE_OVERFLOW;
   }
   GEN_MARK(1);
-  const uint32_t n_q = min((uint32_t)R64(&C.claim_ctr), qcap);
+  const uint32_t n_q = min((uint32_t)C.claim_ctr, qcap);
   auto token_slot = [&](uint32_t i, uint32_t &sl, uint32_t &eps) -> bool {
     bool e, dup;
     qget(i, sl, e, dup);
@@ -392,12 +289,12 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
   // ---- 3 + 4. max-active selection and contraction into the token history ---------------
   float cutoff_eff = cutoff;
   if (abort_code == 0) {
-    const uint32_t nclaim = (uint32_t)(R64(&C.claim_ctr) >> 32);
+    const uint32_t nclaim = (uint32_t)(C.claim_ctr >> 32);
     const uint32_t room = (uint32_t)min((long long)0x7FFFFFFF, D.hist_cap - out_base);
     if ((D.approximate ? nclaim : min(nclaim, (uint32_t)D.max_active)) > room) abort_code = E_HISTORY_OVERFLOW;
     else if (nclaim <= (uint32_t)D.max_active) {
       // nothing can be pruned: every token within the beam is kept
-      for (uint32_t i = gtid; i < n_q; i += gstr) {
+      for (uint32_t i = tid; i < n_q; i += NT) {
         uint32_t sl, eps;
         if (!token_slot(i, sl, eps)) continue;
         Slot *sp = slots + sl;
@@ -410,10 +307,10 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
         hist[out_base + pos] = HTok{sv.handle | (eps ? HAS_EPS : 0u), c, (uint32_t)v, NO_ARC};
         sp->aux = pos;
       }
-      LSYNC();
-      if (lead) C.nvalid = R32(&C.nout);
+      __syncthreads();
+      if (tid == 0) C.nvalid = C.nout;
     } else {
-      for (uint32_t i = gtid; i < n_q; i += gstr) {
+      for (uint32_t i = tid; i < n_q; i += NT) {
         uint32_t sl, eps;
         if (!token_slot(i, sl, eps)) continue;
         const uint32_t key = (uint32_t)(tl64<LDS>(&slots[sl].val) >> 32);
@@ -422,9 +319,9 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
         dkey[p] = key; dslot[p] = sl | (eps ? Q_EPS : 0u);
         atomicMin(&C.kmin, key); atomicMax(&C.kmax, key);
       }
-      LSYNC();
-      const int n = (int)R32(&C.nvalid);
-      const uint32_t kmin = R32(&C.kmin), kmax = R32(&C.kmax);
+      __syncthreads();
+      const int n = (int)C.nvalid;
+      const uint32_t kmin = C.kmin, kmax = C.kmax;
       uint32_t theta = KEY_NONE, h_theta = 0xFFFFFFFFu;       // keep key < theta, or == theta with handle <= h_theta
       auto by_key = [&](int i, uint32_t &v) { v = dkey[i]; return true; };
       auto by_handle_at_theta = [&](int i, uint32_t &v) {
@@ -433,23 +330,19 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
         return true;
       };
       if (n > D.max_active && D.approximate) {
-        uint32_t nl, nq;
-        if constexpr (WIDE) { if (!wide_select<NT>(S, W, sel_pass, n, (uint32_t)D.max_active, kmin, kmax, by_key, theta, nl, nq, true)) { if (tid == 0) S.status = E_DEVICE; __syncthreads(); return; } }
-        else theta = block_histogram_cut<NT>(S, n, (uint32_t)D.max_active, kmin, kmax, by_key);
+        theta = block_histogram_cut<NT>(S, n, (uint32_t)D.max_active, kmin, kmax, by_key);
         cutoff_eff = key2f(theta);                            // (every key <= theta is kept)
       } else if (n > D.max_active) {
         uint32_t n_less, n_eq;
-        if constexpr (WIDE) { if (!wide_select<NT>(S, W, sel_pass, n, (uint32_t)D.max_active, kmin, kmax, by_key, theta, n_less, n_eq, false)) { if (tid == 0) S.status = E_DEVICE; __syncthreads(); return; } }
-        else block_select<NT>(S, n, (uint32_t)D.max_active, kmin, kmax, by_key, theta, n_less, n_eq);
+        block_select<NT>(S, n, (uint32_t)D.max_active, kmin, kmax, by_key, theta, n_less, n_eq);
         const uint32_t need_eq = (uint32_t)D.max_active - n_less;
         if (need_eq < n_eq) {
           uint32_t hl, he;
-          if constexpr (WIDE) { if (!wide_select<NT>(S, W, sel_pass, n, need_eq, 0u, HMASK, by_handle_at_theta, h_theta, hl, he, false)) { if (tid == 0) S.status = E_DEVICE; __syncthreads(); return; } }
-          else block_select<NT>(S, n, need_eq, 0u, HMASK, by_handle_at_theta, h_theta, hl, he);
+          block_select<NT>(S, n, need_eq, 0u, HMASK, by_handle_at_theta, h_theta, hl, he);
         }
         cutoff_eff = key2f(theta);
       }
-      for (uint32_t i = gtid; i < (uint32_t)n; i += gstr) {
+      for (uint32_t i = tid; i < (uint32_t)n; i += NT) {
         const uint32_t key = dkey[i], ds = dslot[i];
         Slot *sp = slots + (ds & Q_SLOT);
         const uint32_t h = tl32<LDS>(&sp->handle);
@@ -465,15 +358,15 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
       }
     }
   }
-  LSYNC();
+  __syncthreads();
   GEN_MARK(2);
-  const uint32_t nout_all = R32(&C.nout);
+  const uint32_t nout_all = C.nout;
   const uint32_t n_out = (abort_code == 0) ? (D.approximate ? nout_all : min(nout_all, (uint32_t)D.max_active)) : 0u;
 
   // ---- 5. lattice records and back-pointers ---------------------------------------------
   if (abort_code == 0) {
     const long long lat_base = S.lat_pos;
-    const uint32_t n_aux = min(R32(&C.auxn), (uint32_t)D.auxcap);
+    const uint32_t n_aux = min(C.auxn, (uint32_t)D.auxcap);
     auto emit_lat = [&](uint32_t arc, float extra, uint32_t dst, uint32_t src) {
       const uint32_t p = wave_alloc(&C.latn);
       if ((long long)p >= S.lat_room) atomicOr(&C.flags, F_LATOVF);
@@ -483,11 +376,11 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
         lat[at] = LatInt{nf, arc, extra, dst, src};
       }
     };
-    for (uint32_t i0 = 0; i0 < n_aux; i0 += gstr * LAT_U) {
+    for (uint32_t i0 = 0; i0 < n_aux; i0 += NT * LAT_U) {
       Aux a[LAT_U];
 #pragma unroll
       for (int u = 0; u < LAT_U; ++u) {
-        const uint32_t i = i0 + (uint32_t)u * gstr + gtid;
+        const uint32_t i = i0 + (uint32_t)u * NT + tid;
         a[u] = i < n_aux ? aux[i] : Aux{0xFFFFFFFFu, 0.f, 0u, 0u};
       }
 #pragma unroll
@@ -526,25 +419,25 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
       }
     }
   }
-  LSYNC();
+  __syncthreads();
   GEN_MARK(3);
 
   // ---- 6. clear the table ---------------------------------------------------------------
-  const uint32_t fl3 = R32(&C.flags);
+  const uint32_t fl3 = C.flags;
   if (fl3 & F_TOKOVF) {                                            // untracked claims: wipe everything
     const uint32_t n_all = D.H;
-    for (uint32_t i = gtid; i < n_all; i += gstr) slots[i] = fresh;
+    for (uint32_t i = tid; i < n_all; i += NT) slots[i] = fresh;
   } else {
-    for (uint32_t i = gtid; i < n_q; i += gstr) {
+    for (uint32_t i = tid; i < n_q; i += NT) {
       uint32_t sl, eps;
       if (token_slot(i, sl, eps)) slots[sl] = fresh;
     }
   }
-  if (tid == 0) {                                   // (every workgroup of the lane keeps its own replica of the lane's state)
+  if (tid == 0) {
     if (abort_code == 0 && (fl3 & F_LATOVF)) abort_code = E_LATTICE_OVERFLOW;
-    const long long lat_new = min((long long)R32(&C.latn), S.lat_room);
+    const long long lat_new = min((long long)C.latn, S.lat_room);
     if (nf <= D.max_frames) {
-      if (wg == 0) foff[nf + 1] = out_base + n_out;
+      foff[nf + 1] = out_base + n_out;
       S.nf = nf + 1;
       S.in_off = out_base; S.n_in = (int)n_out;      // the frame just written is what the next one expands
     }
@@ -552,8 +445,8 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
     S.lat_total += lat_new; S.lat_room -= lat_new;
     S.lat_pos += lat_new;
     if (S.lat_pos >= D.lat_cap) S.lat_pos -= D.lat_cap;
-    S.arcs_expanded += (long long)(R64(&C.emit_arcs) + R64(&C.eps_arcs));
-    S.max_pre = max(S.max_pre, (int)R32(&C.nvalid));
+    S.arcs_expanded += (long long)(C.emit_arcs + C.eps_arcs);
+    S.max_pre = max(S.max_pre, (int)C.nvalid);
     S.max_post = max(S.max_post, (int)n_out);
     S.iters_max = max(S.iters_max, iters);
 #ifdef WFST_PHASE_TIMING
@@ -561,9 +454,8 @@ __device__ void general_frame(const DecDev &D, LaneShared<NT> &S, WideCtx &W, co
 #endif
     if (abort_code != 0) S.status = abort_code;
   }
-  LSYNC();
+  __syncthreads();
   GEN_MARK(4);
-#undef LSYNC
 }
 
 }  // namespace wfst

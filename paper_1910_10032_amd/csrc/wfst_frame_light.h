@@ -62,7 +62,7 @@ __device__ __forceinline__ void count_marks(uint2 *mark, uint32_t n_arcs) {
 
 // Returns false if the frame must be redone by the general frame.
 template <int NT>
-__device__ bool light_frame(const DecDev &D, LaneShared<NT> &S, LaneCtx &ctx, const float *ll, const float *ll_next,
+__device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, LaneCtx &ctx, const float *ll, const float *ll_next,
                             bool is_init, int chan) {
   using L = LightCfg<NT>;
   constexpr int U = L::TILE / NT;
@@ -100,6 +100,11 @@ __device__ bool light_frame(const DecDev &D, LaneShared<NT> &S, LaneCtx &ctx, co
 #pragma unroll 1
     for (int w = tid; w < L::MARK_WORDS; w += NT) { mark_in[w] = make_uint2(0, 0); mark_out[w] = make_uint2(0, 0); }
     if (tid == 0) S.list_dead = 0;
+    if (ctx.lds_foreign) {
+#pragma unroll 1
+      for (int i = tid; i < L::SLOTS; i += NT) slots[i] = fresh;
+      ctx.lds_foreign = false;
+    }
     lds_barrier();
     uint32_t base = 0;
 #pragma unroll 1

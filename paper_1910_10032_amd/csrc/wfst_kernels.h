@@ -31,18 +31,72 @@
 // slower one (the role of the paper's second stream, Section 3, Fig. 1).
 #pragma once
 #include "wfst_frame_general.h"
+#include "wfst_frame_heavy.h"
 #include "wfst_frame_light.h"
 
 namespace wfst {
 
-// One workgroup per lane.  is_init: (re)start the lane's channel and write frame 0.
-// Between frames the lane's state is held in registers by every thread (LaneCtx, all values
-// uniform); a general frame gets it through LDS.
+// Frames without a heavy one after which the extra workgroups of a lane leave (and for how many
+// frames past its last heavy one a channel gets them at the start of a call).
+constexpr int TEAM_PATIENCE = 64;
+
+// An extra workgroup of a lane joins the lane's team, works through the heavy frames the first
+// workgroup calls it to, and leaves when told to.  Nothing depends on it being there: the team is
+// whoever has joined when the first heavy frame comes, so a workgroup that the device has no room
+// for yet finds the team closed when it starts, and leaves.
 template <int NT>
-__global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, const LaneParam *__restrict__ lanes, int is_init) {
-  __shared__ LaneShared<NT> S;
+__device__ __forceinline__ bool team_join(LaneShared<NT> &S, TeamLane *tl, uint32_t launch) {
+  if (threadIdx.x == 0) {
+    uint32_t xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    uint32_t spins = 0;
+    while ((uint32_t)(ld64(&tl->join) >> 32) != launch && ++spins <= TEAM_SPIN_LIMIT) __builtin_amdgcn_s_sleep(2);   // the first workgroup sets the lane up
+    S.team_cmd = 0;
+    if (spins <= TEAM_SPIN_LIMIT) {
+      const uint32_t before = atomicOr(&tl->xcc_mask, 1u << (xcc & 31u));
+      asm volatile("" ::"v"(before));               // (the mask is complete before the count says so)
+      const unsigned long long v = atomicAdd(&tl->join, 1ull);
+      const uint32_t g = (uint32_t)(v & 0xFFFFu) + 1u;
+      if (!(v & TEAM_CLOSED) && g < (uint32_t)TEAM_MAX) { S.team_cmd = 1; S.team.g = (int)g; }
+    }
+  }
+  __syncthreads();
+  return uni(S.team_cmd) != 0;
+}
+// Waits for the next command; false: leave.
+template <int NT>
+__device__ __forceinline__ bool team_next(LaneShared<NT> &S, TeamLane *tl) {
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t polls = 0;
+    const uint32_t seen = S.team.commands;
+    while (ld32(&tl->cmd_seq) == seen && !ld32(&tl->broken) && ++polls != 0xFFFFFFFFu) __builtin_amdgcn_s_sleep(2);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    S.team_cmd = ld32(&tl->cmd_seq) == seen ? (uint32_t)TEAM_EXIT : ld32(&tl->cmd);
+    S.hs = tl->hs;
+    S.team.G = (int)tl->G; S.team.same_xcd = tl->same_xcd; S.team.commands = seen + 1u;
+  }
+  __syncthreads();
+  return uni(S.team_cmd) == (uint32_t)TEAM_FRAME;
+}
+
+// One workgroup per lane, or (TEAM) several: the first n_lanes8 (the number of lanes, rounded up to
+// a multiple of the eight XCDs) blocks are the lanes' first workgroups, the others join them, those
+// of a lane on the same XCD.  is_init: (re)start the lane's channel and write frame 0.
+// Between frames the lane's state is held in registers by every thread (LaneCtx, all values
+// uniform); a general or heavy frame gets it through LDS.
+template <int NT, bool TEAM>
+__global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, const DecDev *Dg, const LaneParam *__restrict__ lanes, int is_init, int n_lanes, int n_lanes8,
+                                                                   uint32_t launch) {
+  LaneShared<NT> &S = lane_lds<NT, TEAM>();
   const int tid = threadIdx.x;
-  LaneParam lp = lanes[blockIdx.x];
+  const bool member = TEAM && (int)blockIdx.x >= n_lanes8;          // an extra workgroup of a lane
+  const int my_lane = uni(member ? ((int)blockIdx.x - n_lanes8) % n_lanes8 : (int)blockIdx.x);
+  if (TEAM && my_lane >= n_lanes) return;
+  TeamLane *const tl = D.teams + my_lane;
+  if (tid == 0) S.team = TeamCtx{tl, 0, 1, 0u, D.team_spin_limit, 0u, 0u, 0u, 0u};
+  if (TEAM && member && !team_join<NT>(S, tl, launch)) return;
+  LaneParam lp = lanes[my_lane];
   lp.ll = (const float *)uni((unsigned long long)lp.ll); lp.chan = uni(lp.chan); lp.n_frames = uni(lp.n_frames); lp.stride = uni(lp.stride);
   lp.snap_every = uni(lp.snap_every); lp.snap_id0 = uni(lp.snap_id0); lp.n_snaps = uni(lp.n_snaps);
   ChanState *cs = D.chan + lp.chan;
@@ -81,7 +135,41 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
     const long long o0 = uni(foff[ctx.nf - 1]), o1 = uni(foff[ctx.nf]);
     ctx.in_off = o0; ctx.n_in = (int)(o1 - o0);
   }
-  ctx.pending_clear = 0; ctx.par = 0; ctx.tok_valid = false; ctx.n_arcs = 0; ctx.n_dead = 0;
+  ctx.pending_clear = 0; ctx.par = 0; ctx.tok_valid = false; ctx.n_arcs = 0; ctx.n_dead = 0; ctx.lds_foreign = false;
+  int last_heavy = is_init ? 0 : uni(cs->last_heavy);
+  // the lane's team: set up, and open to whoever is to join
+  bool team_open = false, team_here = false;        // joining is possible; there are members to call
+  if (TEAM && !member) {
+    for (int i = tid; i < 3 * NBINS; i += NT) tl->hist[0][i] = 0;
+    if (tid == 0) {
+      uint32_t xcc;
+      asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+      tl->xcc_mask = 1u << (xcc & 31u);
+      tl->cmd_seq = 0; tl->cmd = 0; tl->arrived = 0; tl->broken = 0;
+      reset_heavy(tl->ctr[0]); reset_heavy(tl->ctr[1]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      atomicExch(&tl->join, (unsigned long long)launch << 32);
+    }
+    team_open = true;
+  }
+  // (thread 0) nobody joins from here on; how many have
+  auto team_close = [&]() -> uint32_t { return (uint32_t)(atomicOr(&tl->join, TEAM_CLOSED) & 0xFFFFu); };
+  auto team_dismiss = [&]() {
+    if constexpr (TEAM) {
+      if (tid == 0) {
+        if (team_open) (void)team_close();
+        tl->cmd = TEAM_EXIT;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        atomicAdd(&tl->cmd_seq, 1u);
+      }
+      if (tid == 0) S.team.G = 1;                     // (read again after the next barriers only)
+      team_open = false; team_here = false;
+    }
+  };
   __syncthreads();
   // Seal the lane's state as the next snapshot of this call.  With snapshot blocks the lattice
   // records not handed out yet move into the snapshot's block, in the caller's form (the lane
@@ -153,42 +241,102 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
     }
     ++n_sealed;
   };
-  // a frame in the general form: the lane's state goes through LDS
-  auto run_general = [&](const float *ll) {
+  // a frame in the general or heavy form: the lane's state goes through LDS
+  auto state_to_lds = [&]() {
     if (tid == 0) {
       S.status = ctx.status; S.nf = ctx.nf; S.n_in = ctx.n_in; S.max_pre = ctx.max_pre; S.max_post = ctx.max_post;
       S.iters_max = ctx.iters_max; S.in_off = ctx.in_off; S.hist_used = ctx.hist_used; S.lat_room = ctx.lat_room;
       S.lat_total = ctx.lat_total; S.lat_pos = ctx.lat_pos; S.arcs_expanded = ctx.arcs_expanded;
     }
     __syncthreads();                                  // (also: the light frames' history stores have arrived)
-    WideCtx none{0, 1, nullptr, 0ull, 0u};
-    general_frame<NT, false>(D, S, none, ll, is_init != 0, D.slots + (size_t)blockIdx.x * D.H, D.queue + (size_t)blockIdx.x * (size_t)D.qcap,
-                      D.aux + (size_t)blockIdx.x * (size_t)D.auxcap, D.dkey + (size_t)blockIdx.x * (size_t)D.tokcap,
-                      D.dslot + (size_t)blockIdx.x * (size_t)D.tokcap, foff, D.hist + (size_t)lp.chan * (size_t)D.hist_cap, lat);
+  };
+  auto state_from_lds = [&]() {
     ctx.status = uni(S.status); ctx.nf = uni(S.nf); ctx.n_in = uni(S.n_in); ctx.max_pre = uni(S.max_pre); ctx.max_post = uni(S.max_post);
     ctx.iters_max = uni(S.iters_max); ctx.in_off = uni(S.in_off); ctx.hist_used = uni(S.hist_used); ctx.lat_room = uni(S.lat_room);
     ctx.lat_total = uni(S.lat_total); ctx.lat_pos = uni(S.lat_pos); ctx.arcs_expanded = uni(S.arcs_expanded);
     ctx.tok_valid = false;
-    __syncthreads();                                  // all have read the state before the next general frame rewrites it
+    __syncthreads();                                  // all have read the state before the next such frame rewrites it
+  };
+  auto run_general = [&](const float *ll) {
+    state_to_lds();
+    general_frame<NT, TEAM>((ConstDev *)Dg, my_lane, lp.chan, ll, is_init);
+    state_from_lds();
+  };
+  // a frame in the heavy form: what the first workgroup does before it
+  auto call_team = [&](const float *ll) {
+    state_to_lds();
+    if (tid == 0) S.hs = HeavyState{ll, ctx.in_off, ctx.hist_used, ctx.lat_pos, ctx.lat_room, ctx.nf, ctx.n_in};
+    ctx.lds_foreign = true; ctx.tok_valid = false; ctx.pending_clear = 0;
+    if constexpr (TEAM) {
+      if (team_open) {                                // the first heavy frame: the team is whoever has joined
+        if (tid == 0) {
+          const uint32_t want = gridDim.x / (uint32_t)n_lanes8 - 1u;
+          for (uint32_t polls = 0; polls < 64u && (uint32_t)(ld64(&tl->join) & 0xFFFFu) < want; ++polls) __builtin_amdgcn_s_sleep(4);
+          const uint32_t joined = team_close();
+          const uint32_t xccs = ld32(&tl->xcc_mask);
+          S.team.G = (int)joined + 1; S.team.same_xcd = (xccs & (xccs - 1u)) == 0u;
+          tl->G = joined + 1u; tl->same_xcd = S.team.same_xcd;
+        }
+        __syncthreads();
+        team_open = false; team_here = uni(S.team.G) > 1;
+      }
+      __syncthreads();
+      if (team_here && tid == 0) {
+        tl->hs = S.hs;
+        tl->cmd = TEAM_FRAME;
+        if (S.team.same_xcd) asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        atomicAdd(&tl->cmd_seq, 1u);
+      }
+    }
+    __syncthreads();
   };
   const int nframes = is_init ? 1 : lp.n_frames;
   const int n_snaps = is_init ? 0 : lp.n_snaps;
-  const bool light_ok = D.g.info_shift != 0 && D.force_general == 0;
+  const bool light_ok = D.g.info_shift != 0 && D.force_general == 0, heavy_ok = is_init == 0 && D.force_general == 0;
+  if (TEAM && ctx.nf - last_heavy > TEAM_PATIENCE) team_dismiss();
   int until_seal = (!is_init && lp.snap_every > 0) ? lp.snap_every : 0x7FFFFFFF;
   for (int f = 0;;) {
-    const bool more = f < nframes && ctx.status == 0;
+    const bool more = member || (f < nframes && ctx.status == 0);
     if (more) {
-      const float *ll = is_init ? nullptr : lp.ll + (size_t)f * (size_t)lp.stride;
-      const float *ll_next = (!is_init && f + 1 < nframes) ? ll + lp.stride : nullptr;
-      bool done = false;
-      if (light_ok && (is_init || ctx.n_in <= LightCfg<NT>::CLAIM_LIMIT))
-        done = light_frame<NT>(D, S, ctx, ll, ll_next, is_init != 0, lp.chan);
-      if (!done) {
+      const float *ll = nullptr, *ll_next = nullptr;
+      bool done = false, heavy = false;
+      if (member) {
+        if constexpr (TEAM) { if (!team_next<NT>(S, tl)) return; }
+        heavy = true;
+      } else {
+        ll = is_init ? nullptr : lp.ll + (size_t)f * (size_t)lp.stride;
+        ll_next = (!is_init && f + 1 < nframes) ? ll + lp.stride : nullptr;
+        if (light_ok && (is_init || ctx.n_in <= LightCfg<NT>::CLAIM_LIMIT))
+          done = light_frame<NT>(D, S, ctx, ll, ll_next, is_init != 0, lp.chan);
+        if (done) {
+          if (TEAM && (team_open || team_here) && ctx.nf - last_heavy > TEAM_PATIENCE) team_dismiss();
+        } else {
 #ifdef WFST_PHASE_TIMING
-        if (tid == 0) S.ph[6] += 1;
+          if (tid == 0) S.ph[6] += 1;
 #endif
-        run_general(ll);
+          last_heavy = ctx.nf;
+          heavy = heavy_ok;
+          if (heavy) call_team(ll);
+        }
+      }
+      if (heavy) {
+        const int r = uni(heavy_frame<NT, TEAM>((ConstDev *)Dg, my_lane, lp.chan));
+        if (member) {
+          if (r == HEAVY_BROKEN) return;
+          continue;
+        }
+        if (r == HEAVY_BROKEN) {                      // (what the team has written is incomplete: the channel stops)
+          __syncthreads();
+          if (tid == 0) S.status = E_DEVICE;
+          __syncthreads();
+        }
+        done = r != HEAVY_GIVEN_UP;
+        if (done) state_from_lds();
         PHASE_MARK(11);
+      }
+      if (!done) {
+        run_general(ll);
+        PHASE_MARK(10);
       }
 #ifdef WFST_PHASE_TIMING
       if (tid == 0) S.ph[5] += 1;
@@ -203,8 +351,10 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
     seal();
     PHASE_MARK(12);
   }
+  if (TEAM && (team_open || team_here)) team_dismiss();
   __syncthreads();
   if (tid == 0) {
+    cs->last_heavy = last_heavy;
     cs->status = ctx.status; cs->num_frames = ctx.nf; cs->hist_used = ctx.hist_used;
     cs->lat_total = ctx.lat_total; cs->arcs_expanded = ctx.arcs_expanded; cs->max_pre = ctx.max_pre;
     cs->max_post = ctx.max_post; cs->closure_iters_max = ctx.iters_max;
@@ -223,56 +373,6 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
     }
 #endif
   }
-}
-
-// Several workgroups per lane (blockIdx.x = lane * G + g): every frame in the general form, the
-// lane's G workgroups working through it together (see WideCtx).  Every workgroup keeps its own
-// replica of the lane's state; workgroup 0 of the lane writes it back.  For calls with so few
-// lanes that the device would otherwise stand idle; no snapshots.
-template <int NT>
-__global__ void __launch_bounds__(NT, 4) k_advance_wide(DecDev D, const LaneParam *__restrict__ lanes, WideLane *wide, int G) {
-  __shared__ LaneShared<NT> S;
-  const int tid = threadIdx.x;
-  const int lane = blockIdx.x / G, g = blockIdx.x % G;
-  const LaneParam lp = lanes[lane];
-  ChanState *cs = D.chan + lp.chan;
-  long long *foff = D.frame_off + (size_t)lp.chan * (size_t)(D.max_frames + 2);
-  if (tid == 0) {
-    S.status = cs->status; S.nf = cs->num_frames; S.hist_used = cs->hist_used;
-    S.lat_total = cs->lat_total;
-    S.lat_room = D.lat_cap - (cs->lat_total - cs->lat_head);
-    S.lat_pos = cs->lat_total % D.lat_cap;
-    S.arcs_expanded = cs->arcs_expanded; S.max_pre = cs->max_pre; S.max_post = cs->max_post; S.iters_max = cs->closure_iters_max;
-    S.in_off = 0; S.n_in = 0;
-    if (S.nf >= 1 && S.nf <= D.max_frames + 1) { S.in_off = foff[S.nf - 1]; S.n_in = (int)(foff[S.nf] - foff[S.nf - 1]); }
-#ifdef WFST_PHASE_TIMING
-    for (int k = 0; k < 16; ++k) { S.ph[k] = 0; S.gph[k] = 0; }
-    S.dbg_tok = 0; S.dbg_iters = 0; S.dbg_arcs = 0;
-#endif
-  }
-  __syncthreads();
-  WideCtx W{g, G, wide + lane, 0ull, D.wide_spin_limit};
-  for (int f = 0; f < lp.n_frames && S.status == 0; ++f) {
-    general_frame<NT, true>(D, S, W, lp.ll + (size_t)f * (size_t)lp.stride, false, D.slots + (size_t)lane * D.H,
-                            D.queue + (size_t)lane * (size_t)D.qcap, D.aux + (size_t)lane * (size_t)D.auxcap,
-                            D.dkey + (size_t)lane * (size_t)D.tokcap, D.dslot + (size_t)lane * (size_t)D.tokcap, foff,
-                            D.hist + (size_t)lp.chan * (size_t)D.hist_cap, D.lat + (size_t)lp.chan * (size_t)D.lat_cap);
-  }
-  __syncthreads();
-  if (g == 0 && tid == 0) {
-    // (a barrier that was given up leaves the lane's state incomplete: the channel stops with a device error)
-    cs->status = ld32(&wide[lane].broken) && S.status == 0 ? E_DEVICE : S.status;
-    cs->num_frames = S.nf; cs->hist_used = S.hist_used;
-    cs->lat_total = S.lat_total; cs->arcs_expanded = S.arcs_expanded; cs->max_pre = S.max_pre;
-    cs->max_post = S.max_post; cs->closure_iters_max = S.iters_max;
-#ifdef WFST_PHASE_TIMING
-    if (D.dbg) { for (int k = 0; k < 16; ++k) atomicAdd(D.dbg + 16 + 10240 + k, S.gph[k]); atomicAdd(D.dbg + 6, (unsigned long long)lp.n_frames); atomicAdd(D.dbg + 5, (unsigned long long)lp.n_frames); }
-#endif
-  }
-}
-__global__ void k_zero_wide(WideLane *wide, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) { wide[i].arrived = 0ull; wide[i].broken = 0u; }
 }
 
 __global__ void k_fill_slots(Slot *slots, size_t n) {

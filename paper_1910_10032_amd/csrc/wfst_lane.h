@@ -109,6 +109,7 @@ struct LaneCtx {
   long long in_off, hist_used, lat_room, lat_total, lat_pos, lat_head, lat_head_pos, arcs_expanded;
   uint32_t pending_clear;    // states claimed by the last light frame, whose table slots are still to be cleared
   int par;                   // counter set (and set of first-arc marks) the next light frame uses
+  bool lds_foreign;          // a heavy frame has used the light frame's place in LDS
   bool tok_valid;            // the LDS token list holds the frame the next one starts from:
   uint32_t n_arcs, n_dead;   // arc positions its tokens take, and how many of them belong to tokens without an emitting arc
 #ifdef WFST_PHASE_TIMING
@@ -217,13 +218,67 @@ struct GenCtr {
   unsigned long long emit_arcs, eps_arcs;
   uint32_t auxn, best, flags, nvalid, nout, latn, kmin, kmax;
 };
-// A lane shared by several workgroups: its counters, the selection's histogram and the count
-// of workgroups that have arrived at the lane's barriers so far.
-struct WideLane {
-  GenCtr c;
-  uint32_t hist[3][NBINS];     // the selection's passes rotate through three histograms (see wide_select)
-  unsigned long long arrived;
-  uint32_t broken, pad;
+// ---- heavy frames (see wfst_frame_heavy.h) -----------------------------------------------------
+constexpr int TEAM_MAX = 16;                  // workgroups of a lane
+constexpr int HEAVY_LIST = 512;               // (cost, state) pairs that the selection ranks one against the other
+template <int NT> struct HeavyCfg {
+  static constexpr int SLOTS = NT >= 1024 ? 8192 : 4096;   // state table of a workgroup: all the LDS there is
+  static constexpr int HBITS = NT >= 1024 ? 13 : 12;
+  static constexpr int CLAIM_LIMIT = SLOTS * 3 / 4;
+  static constexpr uint32_t MAX_PROBES = 256;
+};
+constexpr uint32_t EL_AGAIN = 0x80000000u;    // in a list of epsilon arcs: listed before, its source has improved since
+constexpr uint32_t EV_FAIL = 0x80000000u, EV_NAN = 0x40000000u, EV_LATOVF = 0x20000000u, EV_COUNT = 0x0FFFFFFFu;
+// What the workgroups of a heavy frame share: in LDS when there is one, in global memory when
+// there are several (then read with loads that bypass the vector cache).
+template <int M> struct HeavyCtr {
+  uint32_t ev[3];              // events of a barrier, and how many candidates were sent before it
+  uint32_t best, nout, latn, kmax, listed;
+  unsigned long long emit[M];  // emitting arcs expanded
+  uint32_t eps[M];             // epsilon out-degrees of the tokens within the beam
+  uint32_t claims[2][M];       // states entered so far (two sets, used at alternate barriers, as the next)
+  uint32_t cnt[2][M][M];       // [owner][sender]: candidates in the bucket
+};
+template <int M> __device__ __forceinline__ void reset_heavy(HeavyCtr<M> &c) {
+  c.ev[0] = 0; c.ev[1] = 0; c.ev[2] = 0;
+  c.best = KEY_NONE; c.nout = 0; c.latn = 0; c.kmax = 0; c.listed = 0;
+}
+struct HeavyState {            // of the lane, as a heavy frame starts from it
+  const float *ll;
+  long long in_off, hist_used, lat_pos, lat_room;
+  int nf, n_in;
+};
+struct HeavyLocal {            // one workgroup's own counters, in LDS
+  unsigned long long ctr;      // epsilon arcs listed << 32 | states claimed
+  uint32_t best, again, fail, lat_full, kept, sent, pos0, pad;
+  uint32_t to[TEAM_MAX];       // candidates put into each owner's bucket
+  uint32_t from[TEAM_MAX], upto[TEAM_MAX];   // of each sender: candidates taken before, and now
+  uint32_t emitted[TEAM_MAX];  // of each sender: emitting candidates
+};
+// A lane with several workgroups, in global memory.
+constexpr unsigned long long TEAM_CLOSED = 1ull << 31;
+enum { TEAM_FRAME = 1, TEAM_EXIT = 2 };
+struct TeamLane {
+  unsigned long long join;     // launch << 32 | TEAM_CLOSED | workgroups that have joined
+  uint32_t xcc_mask;           // the XCDs they run on
+  uint32_t cmd_seq, cmd;       // commands given so far, and the last one
+  uint32_t arrived, broken;    // barriers
+  uint32_t G, same_xcd;
+  HeavyState hs;
+  HeavyCtr<TEAM_MAX> ctr[2];   // used by alternate frames
+  uint32_t hist[3][NBINS];     // the selection's passes rotate through three histograms: pass p counts into
+                               // p % 3 and zeroes (p + 2) % 3, which nobody reads any more
+};
+
+struct TeamCtx {               // a workgroup's place in its lane's team, in its LDS
+  TeamLane *tl;
+  int g, G;                    // its number, and how many there are
+  uint32_t epoch;              // arrivals expected at the next barrier (thread 0 keeps count)
+  uint32_t spin_limit;
+  uint32_t seq;                // frames the team has worked through
+  uint32_t pass;               // histogram passes so far (same in all workgroups)
+  uint32_t same_xcd;
+  uint32_t commands;           // of the lane's first workgroup, seen so far
 };
 
 // LDS of a lane's workgroup.
@@ -240,7 +295,6 @@ struct LaneShared {
   //    frames the state lives in registers, see LaneCtx)
   GenCtr gen;                  // the general frame's counters (one workgroup per lane)
   uint32_t sel_bin, sel_below, sel_cnt;
-  uint32_t wide_ok;            // outcome of the last lane barrier (lanes shared by several workgroups)
   int status, nf, max_pre, max_post, iters_max, n_in;
   long long in_off, hist_used, lat_room, lat_total, arcs_expanded;
   long long lat_pos;           // ring position of record number lat_total
@@ -248,19 +302,39 @@ struct LaneShared {
 #ifdef WFST_PHASE_TIMING
   unsigned long long ph[16], gph[16], gtlast, dbg_tok, dbg_iters, dbg_arcs;
 #endif
-  // -- light frame
-  FrameCtr fc[2];
-  uint2 tok[LightCfg<NT>::CLAIM_LIMIT];        // kept tokens of the last frame = queue of the next: state handle | TOK_DEAD, cost
-  uint16_t tok_a[LightCfg<NT>::CLAIM_LIMIT];   //   position of the token's first arc among the frame's arcs
-  uint2 mark[2][LightCfg<NT>::MARK_WORDS];     // arc positions at which a token's arcs begin (bits), and their number in the words before
+  FrameCtr fc[2];              // light frames
   uint32_t list_dead;
-  uint16_t lq[LightCfg<NT>::CLAIM_LIMIT];      // claimed slots, in the order of their tokens
-  uint32_t ea_r[LightCfg<NT>::ECAP];           // epsilon arcs to relax: arc,
-  float ea_w[LightCfg<NT>::ECAP];              //   weight (once fetched),
-  uint16_t ea_s[LightCfg<NT>::ECAP];           //   slot of the source | EA_AGAIN,
-  uint16_t ea_d[LightCfg<NT>::ECAP];           //   slot of the destination, 0xFFFF if the candidate was beyond the cutoff
-  Slot table[LightCfg<NT>::SLOTS];             // state table
+  HeavyCtr<1> hc;              // heavy frames
+  HeavyLocal hl;
+  HeavyState hs;
+  TeamCtx team;
+  uint32_t team_ok, team_cmd;
+  unsigned long long sel_theta;
+  union {
+    struct {                   // -- light frame
+      uint2 tok[LightCfg<NT>::CLAIM_LIMIT];        // kept tokens of the last frame = queue of the next: state handle | TOK_DEAD, cost
+      uint16_t tok_a[LightCfg<NT>::CLAIM_LIMIT];   //   position of the token's first arc among the frame's arcs
+      uint2 mark[2][LightCfg<NT>::MARK_WORDS];     // arc positions at which a token's arcs begin (bits), and their number in the words before
+      uint16_t lq[LightCfg<NT>::CLAIM_LIMIT];      // claimed slots, in the order of their tokens
+      uint32_t ea_r[LightCfg<NT>::ECAP];           // epsilon arcs to relax: arc,
+      float ea_w[LightCfg<NT>::ECAP];              //   weight (once fetched),
+      uint16_t ea_s[LightCfg<NT>::ECAP];           //   slot of the source | EA_AGAIN,
+      uint16_t ea_d[LightCfg<NT>::ECAP];           //   slot of the destination, 0xFFFF if the candidate was beyond the cutoff
+      Slot table[LightCfg<NT>::SLOTS];             // state table
+    };
+    struct {                   // -- heavy frame
+      Slot table[HeavyCfg<NT>::SLOTS];
+      uint16_t lq[HeavyCfg<NT>::CLAIM_LIMIT];      // claimed slots
+    } hv;
+  };
 };
+
+// The workgroup's LDS block.  (Functions that are not inlined name it themselves: a reference
+// handed to them would be a generic pointer.)
+template <int NT, bool TEAM> __device__ __forceinline__ LaneShared<NT> &lane_lds() {
+  static __shared__ LaneShared<NT> S;
+  return S;
+}
 
 #ifdef WFST_PHASE_TIMING
 // (instrumented builds) thread 0 adds the time since its previous mark to phase k
