@@ -18,6 +18,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # the loop over a lane's frames is one big loop: hoisting every loop-invariant move out of it
+           # fills the registers and spills what the frame itself needs (156 bytes per thread, some of them
+           # reloaded in every closure round; none without)
+           "-mllvm", "-disable-machine-licm",
            "-fPIC", "-shared", "-o", LIB] + SOURCES
     if verbose:
         cmd += ["-Rpass-analysis=kernel-resource-usage"]

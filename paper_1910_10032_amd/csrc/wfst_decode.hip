@@ -25,6 +25,8 @@ static_assert(sizeof(TokOut) == sizeof(wfst_token_t), "token layout");
 static_assert(sizeof(Slot) == 16 && sizeof(HTok) == 16 && sizeof(Aux) == 16, "16-byte records");
 
 constexpr int NT = 512;          // threads of the workgroup that owns a lane
+constexpr int TEAM_MEMORY = 8;   // calls after one with heavy frames for which lanes get teams
+constexpr int TEAM_AUTO = 8;     // workgroups of a team by the library's choice (400 frames of 42 000 arcs: 4 / 8 / 16 -> 42.9 / 32.9 / 35.2 ms)
 constexpr int NUM_XCDS = 8;      // the dispatcher deals workgroups to them in turn
 constexpr int PARAM_RING = 8;    // pinned buffers for lane parameters
 constexpr size_t PINNED_WORDS_BYTES = (size_t)16 << 20;   // best-path words of a readout that go straight to pinned host memory
@@ -69,7 +71,10 @@ struct wfst_decoder {
   hipStream_t last_stream = nullptr;    // stream of the last advance call; readouts use it
   hipEvent_t last_advance = nullptr;    // recorded behind the last advance call
   bool have_last_advance = false;
+  int32_t last_lanes = 0;               // lanes of the last advance call
   hipStream_t side_stream = nullptr;    // snapshot readouts run here, beside the decoding
+  int32_t *h_heavy = nullptr;           // [max_lanes], in h_pinned: frames of a lane's last call that were not light
+  int heavy_calls = 1;        // calls for which lanes still get teams, unless another one has such frames
   long long *h_sealed = nullptr;        // [max_lanes], in h_pinned: id of the last snapshot each lane sealed
   int64_t next_snap_id = 1;
   struct SnapCall { int64_t id0; int32_t n_snaps, n_lanes; hipStream_t stream; };
@@ -156,13 +161,27 @@ int check_channels(wfst_decoder *d, const int32_t *channels, int32_t n, bool nee
 // How many workgroups a lane gets when a call has n lanes: as many as the device has compute units
 // for, on one XCD with each other (lane i of a call runs on XCD i % 8), but no more than TEAM_MAX and
 // no more than the configuration allows (0: the library's choice).  They help with heavy frames
-// only; a lane that has had none for a while sends them away.
-int lane_team(const wfst_decoder *d, int n) {
+// only; a lane that has had none for a while sends them away.  Where light frames are the rule they
+// still cost something (about 15 us per call to set up and take down, and 1 us per frame: the kernel
+// with teams has fewer registers to spare), so by the library's choice lanes get them only while
+// heavy frames have been seen in the decoder's last TEAM_MEMORY calls, or nothing is known yet.
+int lane_team(wfst_decoder *d, int n) {
   const wfst_config_t &c = d->cfg;
   const int per_xcd = d->num_cus / NUM_XCDS, lanes_per_xcd = (n + NUM_XCDS - 1) / NUM_XCDS;
-  const int most = c.lane_workgroups == 0 ? TEAM_MAX : std::min(c.lane_workgroups, TEAM_MAX);
+  const int most = c.lane_workgroups == 0 ? TEAM_AUTO : std::min(c.lane_workgroups, TEAM_MAX);
   if (c.lane_workgroups <= 1 && (c.lane_workgroups == 1 || (c.lane_threads != 0 && c.lane_threads != 1024))) return 1;
   if (c.frame_form != 0 || n > d->team_lanes) return 1;
+  if (c.lane_workgroups == 0) {
+    const bool over = d->have_last_advance && hipEventQuery(d->last_advance) == hipSuccess;
+    (void)hipGetLastError();                           // ("not ready" is no error)
+    if (over) {                                        // (what a call still running finds out counts later)
+      int32_t seen = 0;
+      for (int32_t i = 0; i < d->last_lanes; ++i) seen |= __atomic_load_n(&d->h_heavy[i], __ATOMIC_RELAXED);
+      if (seen) d->heavy_calls = TEAM_MEMORY;
+      else if (d->heavy_calls > 0) --d->heavy_calls;
+    }
+    if (d->heavy_calls == 0) return 1;
+  }
   return std::max(1, std::min(most, per_xcd / lanes_per_xcd));
 }
 
@@ -447,7 +466,7 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
     // one pinned allocation: the ring of lane parameters, then the lanes' progress words
     const size_t ring_bytes = PARAM_RING * sizeof(LaneParam) * nl;
     void *pinned_dev = nullptr;
-    ok = ok && hipHostMalloc(&d->h_pinned, ring_bytes + sizeof(long long) * nl) == hipSuccess &&
+    ok = ok && hipHostMalloc(&d->h_pinned, ring_bytes + (sizeof(long long) + sizeof(int32_t)) * nl) == hipSuccess &&
          hipHostGetDevicePointer(&pinned_dev, d->h_pinned, 0) == hipSuccess;
     for (int i = 0; ok && i < PARAM_RING; ++i) {
       d->h_params[i] = (LaneParam *)d->h_pinned + (size_t)i * nl;
@@ -462,6 +481,9 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
       d->h_sealed = (long long *)((char *)d->h_pinned + ring_bytes);
       D.lane_sealed = (long long *)((char *)pinned_dev + ring_bytes);
       std::memset(d->h_sealed, 0, sizeof(long long) * nl);
+      d->h_heavy = (int32_t *)(d->h_sealed + nl);
+      D.lane_heavy = (int32_t *)(D.lane_sealed + nl);
+      std::memset(d->h_heavy, 0, sizeof(int32_t) * nl);
     }
     ok = ok && hipMalloc((void **)&d->d_dev, sizeof(DecDev)) == hipSuccess && hipMemcpy(d->d_dev, &D, sizeof(DecDev), hipMemcpyHostToDevice) == hipSuccess;
     if (ok) {
@@ -575,6 +597,7 @@ static int advance_impl(wfst_decoder_t *d, const int32_t *channels, int32_t n_la
   if (rc) return rc;
   HIP_TRY(hipEventRecord(d->last_advance, (hipStream_t)stream));
   d->have_last_advance = true;
+  d->last_lanes = n_lanes;
   if (n_snaps > 0) {
     d->next_snap_id += n_snaps;
     d->snap_calls.push_back({id0, n_snaps, n_lanes, (hipStream_t)stream});

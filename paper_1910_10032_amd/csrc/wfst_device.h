@@ -128,6 +128,7 @@ struct DecDev {
   ChanState *chan;
   ChanSnap *snap;            // [num_channels][SNAP_RING]
   long long *lane_sealed;    // [max_lanes] pinned host memory: id of the last snapshot a lane sealed
+  int32_t *lane_heavy;       // [max_lanes] pinned host memory: frames of a lane's last call that were not light
   SnapBlock *blk;            // [n_blk] snapshot id -> block id % n_blk
   LatRec *blk_recs;          // [n_blk][blk_cap]
   long long blk_cap;

@@ -112,7 +112,7 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
       const int i = tb + tid;
       int a = 0;                               // arc positions the token takes (one if it has no emitting arc)
       if (i < n_in) {
-        const HTok t = hist[ctx.in_off + i];
+        const HTok t = hist[ctx.hist_used - n_in + i];
         const uint32_t h = t.handle & HMASK, ne = rec[3 * (size_t)h];
         S.tok[i] = make_uint2(h | (ne ? 0u : TOK_DEAD), __float_as_uint(t.cost));
         if (!ne) atomicAdd(&S.list_dead, 1u);
@@ -513,7 +513,7 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
   // Every arc into a kept token within the effective cutoff and the lattice beam is recorded
   // with its extra cost (Section 3.4).
   if (abort_code == 0) {
-    const long long lat_base = ctx.lat_pos, lat_room = ctx.lat_room;
+    const long long lat_base = ctx.lat_pos, lat_room = D.lat_cap - ctx.lat_pend;
     auto emit_lat = [&](uint32_t p, uint32_t arc, float extra, uint32_t dst, uint32_t src) {
       if ((long long)p >= lat_room) atomicOr(&C.flags, F_LATOVF);
       else {
@@ -619,19 +619,21 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
   // ---- 6. the lane's state after the frame (every thread computes the same values) -----------
   const uint4 ends = *reinterpret_cast<const uint4 *>(&C.flags);   // flags, latn, dead, again
   if (abort_code == 0 && (uni(ends.x) & F_LATOVF)) abort_code = E_LATTICE_OVERFLOW;
-  const long long lat_new = min((long long)uni(ends.y), ctx.lat_room);
-  if (tid == 0) (D.frame_off + (size_t)chan * (size_t)(D.max_frames + 2))[nf + 1] = out_base + n_out;
+  const long long lat_new = min((long long)uni(ends.y), D.lat_cap - ctx.lat_pend);
+  if (tid == NT - 1) {                         // (of the wave least likely to have had arcs)
+    (D.frame_off + (size_t)chan * (size_t)(D.max_frames + 2))[nf + 1] = out_base + n_out;
+    S.arcs_expanded += (long long)(total - (is_init ? 0 : (int)ctx.n_dead)) + (n_valid ? (long long)(e_hi - ends.w) : 0ll);
+    S.max_pre = max(S.max_pre, (int)n_valid);
+    S.max_post = max(S.max_post, (int)n_out);
+    S.iters_max = max(S.iters_max, iters);
+  }
   ctx.nf = nf + 1;
-  ctx.arcs_expanded += (long long)(total - (is_init ? 0 : (int)ctx.n_dead)) + (n_valid ? (long long)(e_hi - uni(ends.w)) : 0ll);
-  ctx.in_off = out_base; ctx.n_in = (int)n_out;
+  ctx.n_in = (int)n_out;
   ctx.n_arcs = narcs; ctx.n_dead = uni(ends.z);
   ctx.hist_used = out_base + n_out;
-  ctx.lat_total += lat_new; ctx.lat_room -= lat_new;
+  ctx.lat_total += lat_new; ctx.lat_pend += lat_new;
   ctx.lat_pos += lat_new;
   if (ctx.lat_pos >= D.lat_cap) ctx.lat_pos -= D.lat_cap;
-  ctx.max_pre = max(ctx.max_pre, (int)n_valid);
-  ctx.max_post = max(ctx.max_post, (int)n_out);
-  ctx.iters_max = max(ctx.iters_max, iters);
 #ifdef WFST_PHASE_TIMING
   if (tid == 0) { S.ph[7] += iters; S.dbg_tok += n_out; }
 #endif

@@ -119,24 +119,20 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
   ctx.tlast = wall_clock64();
 #endif
   if (is_init) {
-    ctx.status = 0; ctx.nf = 0; ctx.hist_used = 0; ctx.lat_room = D.lat_cap; ctx.lat_pos = 0; ctx.lat_total = 0;
-    ctx.arcs_expanded = 0; ctx.lat_head = 0; ctx.lat_head_pos = 0; ctx.max_pre = 0; ctx.max_post = 0; ctx.iters_max = 0;
+    ctx.status = 0; ctx.nf = 0; ctx.hist_used = 0; ctx.lat_pend = 0; ctx.lat_pos = 0; ctx.lat_total = 0;
+    if (tid == 0) { S.arcs_expanded = 0; S.max_pre = 0; S.max_post = 0; S.iters_max = 0; }
   } else {
     ctx.status = uni(cs->status); ctx.nf = uni(cs->num_frames); ctx.hist_used = uni(cs->hist_used);
-    ctx.lat_head = uni(cs->lat_head); ctx.lat_total = uni(cs->lat_total);
-    ctx.lat_room = D.lat_cap - (ctx.lat_total - ctx.lat_head);
+    ctx.lat_total = uni(cs->lat_total);
+    ctx.lat_pend = ctx.lat_total - uni(cs->lat_head);
     ctx.lat_pos = ctx.lat_total % D.lat_cap;
-    ctx.lat_head_pos = ctx.lat_head % D.lat_cap;
-    ctx.arcs_expanded = uni(cs->arcs_expanded); ctx.max_pre = uni(cs->max_pre);
-    ctx.max_post = uni(cs->max_post); ctx.iters_max = uni(cs->closure_iters_max);
+    if (tid == 0) { S.arcs_expanded = cs->arcs_expanded; S.max_pre = cs->max_pre; S.max_post = cs->max_post; S.iters_max = cs->closure_iters_max; }
   }
-  ctx.in_off = 0; ctx.n_in = 0;
-  if (!is_init && ctx.nf >= 1 && ctx.nf <= D.max_frames + 1) {
-    const long long o0 = uni(foff[ctx.nf - 1]), o1 = uni(foff[ctx.nf]);
-    ctx.in_off = o0; ctx.n_in = (int)(o1 - o0);
-  }
+  ctx.n_in = 0;
+  if (!is_init && ctx.nf >= 1 && ctx.nf <= D.max_frames + 1) ctx.n_in = (int)(uni(foff[ctx.nf]) - uni(foff[ctx.nf - 1]));
   ctx.pending_clear = 0; ctx.par = 0; ctx.tok_valid = false; ctx.n_arcs = 0; ctx.n_dead = 0; ctx.lds_foreign = false;
   int last_heavy = is_init ? 0 : uni(cs->last_heavy);
+  int n_heavy = 0, gave_up = 0x7FFFFFFF;             // frames that were not light; tokens of the last frame whose heavy form was given up
   // the lane's team: set up, and open to whoever is to join
   bool team_open = false, team_here = false;        // joining is possible; there are members to call
   if (TEAM && !member) {
@@ -184,7 +180,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
     long long blk_start = 0, blk_count = 0;
     if (D.n_blk > 0 && D.lattice_on) {
       const int slot = (int)(id % D.n_blk);
-      const long long n = ctx.lat_total - ctx.lat_head;
+      const long long n = ctx.lat_pend;
       if (tid == 0) {
         unsigned long long *used = &D.blk[slot].used;
         unsigned long long old = ld64(used);
@@ -201,7 +197,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
       if (pos < 0 && ctx.status == 0) ctx.status = E_LATTICE_OVERFLOW;
       if (pos >= 0) {
         LatRec *out = D.blk_recs + (size_t)slot * (size_t)D.blk_cap + (size_t)pos;
-        const long long first = ctx.lat_head_pos;
+        const long long first = ctx.lat_pos >= n ? ctx.lat_pos - n : ctx.lat_pos - n + D.lat_cap;
         constexpr int U = 8;                            // records per thread in flight: the arc-id gathers are HBM round trips
         for (long long i0 = tid; i0 < n; i0 += (long long)NT * U) {
           LatInt r[U];
@@ -223,7 +219,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
         }
         blk_start = pos; blk_count = n;
       }
-      ctx.lat_head = ctx.lat_total; ctx.lat_head_pos = ctx.lat_pos; ctx.lat_room = D.lat_cap;
+      ctx.lat_pend = 0;
     }
     // Every thread's stores (tokens, lattice records, the block) must have reached the L2 before
     // thread 0 publishes: each wave waits until its own stores have been acknowledged, then the
@@ -244,16 +240,14 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
   // a frame in the general or heavy form: the lane's state goes through LDS
   auto state_to_lds = [&]() {
     if (tid == 0) {
-      S.status = ctx.status; S.nf = ctx.nf; S.n_in = ctx.n_in; S.max_pre = ctx.max_pre; S.max_post = ctx.max_post;
-      S.iters_max = ctx.iters_max; S.in_off = ctx.in_off; S.hist_used = ctx.hist_used; S.lat_room = ctx.lat_room;
-      S.lat_total = ctx.lat_total; S.lat_pos = ctx.lat_pos; S.arcs_expanded = ctx.arcs_expanded;
+      S.status = ctx.status; S.nf = ctx.nf; S.n_in = ctx.n_in; S.in_off = ctx.hist_used - ctx.n_in; S.hist_used = ctx.hist_used;
+      S.lat_room = D.lat_cap - ctx.lat_pend; S.lat_total = ctx.lat_total; S.lat_pos = ctx.lat_pos;
     }
     __syncthreads();                                  // (also: the light frames' history stores have arrived)
   };
   auto state_from_lds = [&]() {
-    ctx.status = uni(S.status); ctx.nf = uni(S.nf); ctx.n_in = uni(S.n_in); ctx.max_pre = uni(S.max_pre); ctx.max_post = uni(S.max_post);
-    ctx.iters_max = uni(S.iters_max); ctx.in_off = uni(S.in_off); ctx.hist_used = uni(S.hist_used); ctx.lat_room = uni(S.lat_room);
-    ctx.lat_total = uni(S.lat_total); ctx.lat_pos = uni(S.lat_pos); ctx.arcs_expanded = uni(S.arcs_expanded);
+    ctx.status = uni(S.status); ctx.nf = uni(S.nf); ctx.n_in = uni(S.n_in); ctx.hist_used = uni(S.hist_used);
+    ctx.lat_pend = D.lat_cap - uni(S.lat_room); ctx.lat_total = uni(S.lat_total); ctx.lat_pos = uni(S.lat_pos);
     ctx.tok_valid = false;
     __syncthreads();                                  // all have read the state before the next such frame rewrites it
   };
@@ -265,7 +259,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
   // a frame in the heavy form: what the first workgroup does before it
   auto call_team = [&](const float *ll) {
     state_to_lds();
-    if (tid == 0) S.hs = HeavyState{ll, ctx.in_off, ctx.hist_used, ctx.lat_pos, ctx.lat_room, ctx.nf, ctx.n_in};
+    if (tid == 0) S.hs = HeavyState{ll, ctx.hist_used - ctx.n_in, ctx.hist_used, ctx.lat_pos, D.lat_cap - ctx.lat_pend, ctx.nf, ctx.n_in};
     ctx.lds_foreign = true; ctx.tok_valid = false; ctx.pending_clear = 0;
     if constexpr (TEAM) {
       if (team_open) {                                // the first heavy frame: the team is whoever has joined
@@ -315,7 +309,9 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
           if (tid == 0) S.ph[6] += 1;
 #endif
           last_heavy = ctx.nf;
-          heavy = heavy_ok;
+          ++n_heavy;
+          // (a frame that starts from nearly as many tokens as one that did not fit will not fit either)
+          heavy = heavy_ok && (long long)ctx.n_in * 8 < (long long)gave_up * 7;
           if (heavy) call_team(ll);
         }
       }
@@ -331,6 +327,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
           __syncthreads();
         }
         done = r != HEAVY_GIVEN_UP;
+        gave_up = done ? 0x7FFFFFFF : ctx.n_in;
         if (done) state_from_lds();
         PHASE_MARK(11);
       }
@@ -355,11 +352,12 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
   __syncthreads();
   if (tid == 0) {
     cs->last_heavy = last_heavy;
+    if (!is_init) D.lane_heavy[my_lane] = n_heavy;
     cs->status = ctx.status; cs->num_frames = ctx.nf; cs->hist_used = ctx.hist_used;
-    cs->lat_total = ctx.lat_total; cs->arcs_expanded = ctx.arcs_expanded; cs->max_pre = ctx.max_pre;
-    cs->max_post = ctx.max_post; cs->closure_iters_max = ctx.iters_max;
+    cs->lat_total = ctx.lat_total; cs->arcs_expanded = S.arcs_expanded; cs->max_pre = S.max_pre;
+    cs->max_post = S.max_post; cs->closure_iters_max = S.iters_max;
     if (is_init) cs->path_nf = 0;
-    cs->lat_head = ctx.lat_head;
+    cs->lat_head = ctx.lat_total - ctx.lat_pend;
 #ifdef WFST_PHASE_TIMING
     if (D.dbg) {
       for (int k = 0; k < 16; ++k) { atomicAdd(D.dbg + k, S.ph[k]); atomicAdd(D.dbg + 16 + 10240 + k, S.gph[k]); }

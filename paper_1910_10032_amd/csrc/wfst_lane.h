@@ -103,10 +103,16 @@ __device__ __forceinline__ void reset_ctr(FrameCtr &c) {
   c.kmin = 0xFFFFFFFFu; c.kmax = 0;
 }
 
-// State of a lane that every thread of its workgroup holds in registers (all values uniform).
+// State of a lane that every thread of its workgroup holds in registers (all values uniform; as
+// little as possible, since scalar registers are what the light frame runs out of).  What is only
+// counted is in LDS (LaneShared::arcs_expanded, max_pre, max_post, iters_max), kept by one thread.
 struct LaneCtx {
-  int status, nf, n_in, max_pre, max_post, iters_max;
-  long long in_off, hist_used, lat_room, lat_total, lat_pos, lat_head, lat_head_pos, arcs_expanded;
+  int status, nf;
+  int n_in;                  // tokens of the last frame: [hist_used - n_in, hist_used) of the history
+  long long hist_used;
+  long long lat_total;       // lattice records produced since init,
+  long long lat_pend;        //   of which not handed out yet,
+  long long lat_pos;         //   and the ring position of the next one
   uint32_t pending_clear;    // states claimed by the last light frame, whose table slots are still to be cleared
   int par;                   // counter set (and set of first-arc marks) the next light frame uses
   bool lds_foreign;          // a heavy frame has used the light frame's place in LDS
