@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
   if (tid == 0) S.team = TeamCtx{tl, 0, 1, 0u, D.team_spin_limit, 0u, 0u, 0u, 0u};
   if (TEAM && member && !team_join<NT>(S, tl, launch)) return;
   LaneParam lp = lanes[my_lane];
-  lp.ll = (const float *)uni((unsigned long long)lp.ll); lp.chan = uni(lp.chan); lp.n_frames = uni(lp.n_frames); lp.stride = uni(lp.stride);
+  lp.ll = (const float *)(__attribute__((address_space(1))) const float *)uni((unsigned long long)lp.ll); lp.chan = uni(lp.chan); lp.n_frames = uni(lp.n_frames); lp.stride = uni(lp.stride);
   lp.snap_every = uni(lp.snap_every); lp.snap_id0 = uni(lp.snap_id0); lp.n_snaps = uni(lp.n_snaps);
   ChanState *cs = D.chan + lp.chan;
   long long *foff = D.frame_off + (size_t)lp.chan * (size_t)(D.max_frames + 2);
