@@ -30,7 +30,6 @@ constexpr int TEAM_AUTO = 8;     // workgroups of a team by the library's choice
 constexpr int NUM_XCDS = 8;      // the dispatcher deals workgroups to them in turn
 constexpr int PARAM_RING = 8;    // pinned buffers for lane parameters
 constexpr size_t PINNED_WORDS_BYTES = (size_t)16 << 20;   // best-path words of a readout that go straight to pinned host memory
-constexpr int PATH_SNAP_W = 16;  // threads per channel of a best-path readout beside a running decode kernel
 
 struct wfst_graph {
   GraphDev dev{};
@@ -701,12 +700,8 @@ static int best_path_batch_impl(wfst_decoder_t *d, int64_t snap, const int32_t *
   int32_t *const d_words = direct ? (int32_t *)((char *)d->d_pin + head) : (int32_t *)d->d_stage;
   if (!direct) HIP_TRY(hipMemsetAsync(d->d_cnt, 0, sizeof(unsigned long long), st));
   unsigned long long *const used_ctr = direct ? nullptr : d->d_cnt;
-  if (snap > 0)      // beside a running decode kernel: few waves
-    hipLaunchKernelGGL(k_best_path_words<PATH_SNAP_W>, dim3((n * PATH_SNAP_W + 63) / 64), dim3(64), 0, st, d->dev, (const int32_t *)d->d_chans, n,
-                       use_final, sn, d_words, words_cap, used_ctr, d_po);
-  else
-    hipLaunchKernelGGL(k_best_path_words<64>, dim3(n), dim3(64), 0, st, d->dev, (const int32_t *)d->d_chans, n,
-                       use_final, sn, d_words, words_cap, used_ctr, d_po);
+  hipLaunchKernelGGL(k_best_path_words, dim3(n), dim3(64), 0, st, d->dev, (const int32_t *)d->d_chans, use_final, sn, d_words, words_cap,
+                     used_ctr, d_po);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(st));
   const int32_t *w = (const int32_t *)((const char *)d->h_pin + head);

@@ -8,12 +8,13 @@ namespace wfst {
 // the lane's global scratch, tokens and state headers read from memory.  It handles frames of
 // any size (up to the decoder's capacities) and every graph; what fits the LDS forms takes those
 // (wfst_frame_light.h, wfst_frame_heavy.h).  Stages as listed at the top of wfst_kernels.h.
-// (A function of its own, as the heavy frame.)
+// (Inputs hidden from the compiler, as the heavy frame's.)
 template <int NT, bool TEAM>
-__device__ __attribute__((noinline)) void general_frame(ConstDev *Dp, int my_lane, int chan, const float *ll, int is_init) {
+__device__ __forceinline__ void general_frame(ConstDev *Dp, int my_lane, int chan, const float *ll, int is_init) {
+  asm volatile("" : "+s"(Dp), "+s"(my_lane), "+s"(chan));
   ConstDev &D = *(ConstDev *)uni((unsigned long long)Dp);
   LaneShared<NT> &S = lane_lds<NT, TEAM>();
-  my_lane = uni(my_lane); chan = uni(chan); ll = (const float *)uni((unsigned long long)ll); is_init = uni(is_init);
+  my_lane = uni(my_lane); chan = uni(chan); ll = uni(ll); is_init = uni(is_init);
   Slot *const gslots = D.slots + (size_t)my_lane * D.H;
   uint32_t *const queue = D.queue + (size_t)my_lane * (size_t)D.qcap;
   Aux *const aux = D.aux + (size_t)my_lane * (size_t)D.auxcap;
@@ -21,7 +22,8 @@ __device__ __attribute__((noinline)) void general_frame(ConstDev *Dp, int my_lan
   long long *const foff = D.frame_off + (size_t)chan * (size_t)(D.max_frames + 2);
   HTok *const hist = D.hist + (size_t)chan * (size_t)D.hist_cap;
   LatInt *const lat = D.lat + (size_t)chan * (size_t)D.lat_cap;
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   GenCtr &C = S.gen;
   const uint32_t *rec = D.g.rec;
   constexpr bool LDS = false;                // table words are read with coherent global loads

@@ -64,10 +64,11 @@ enum { HEAVY_DONE = 0, HEAVY_GIVEN_UP = 1, HEAVY_BROKEN = 2 };
 
 // One frame; the lane's state is in S.hs (and, of the first workgroup, the rest of it in S).  The
 // lane's scratch: aux / infos hold the buckets' entries, er / es the lists of epsilon arcs.
-// (A function of its own, so that it has the registers to itself and takes none from the light frame.)
+// (Its inputs are hidden from the compiler, so that it takes no registers from the light frame; see k_advance.)
 template <int NT, bool TEAM>
-__device__ __attribute__((noinline)) int heavy_frame(ConstDev *Dp, int my_lane, int chan) {
+__device__ __forceinline__ int heavy_frame(ConstDev *Dp, int my_lane, int chan) {
   using HC = HeavyCfg<NT>;
+  asm volatile("" : "+s"(Dp), "+s"(my_lane), "+s"(chan));
   ConstDev &D = *(ConstDev *)uni((unsigned long long)Dp);
   LaneShared<NT> &S = lane_lds<NT, TEAM>();
   my_lane = uni(my_lane); chan = uni(chan);
@@ -83,7 +84,8 @@ __device__ __attribute__((noinline)) int heavy_frame(ConstDev *Dp, int my_lane, 
   constexpr uint32_t mask = HC::SLOTS - 1;
   constexpr int hbits = HC::HBITS;
   constexpr int U = 4;
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wid = uni(tid >> 6);
   const unsigned long long below = (1ull << lane) - 1ull;
   const uint32_t G = TEAM ? (uint32_t)W.G : 1u, g = TEAM ? (uint32_t)W.g : 0u;
@@ -92,7 +94,7 @@ __device__ __attribute__((noinline)) int heavy_frame(ConstDev *Dp, int my_lane, 
   const bool lead = g == 0 && tid == 0;
   const uint32_t *rec = D.g.rec;
   HeavyState hs = S.hs;                             // (the same for every thread: in scalar registers)
-  hs.ll = (const float *)uni((unsigned long long)hs.ll); hs.in_off = uni(hs.in_off); hs.hist_used = uni(hs.hist_used);
+  hs.ll = uni(hs.ll); hs.in_off = uni(hs.in_off); hs.hist_used = uni(hs.hist_used);
   hs.lat_pos = uni(hs.lat_pos); hs.lat_room = uni(hs.lat_room); hs.nf = uni(hs.nf); hs.n_in = uni(hs.n_in);
   Slot *slots = S.hv.table;
   HeavyLocal &H = S.hl;

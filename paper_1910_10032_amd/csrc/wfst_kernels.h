@@ -85,19 +85,28 @@ __device__ __forceinline__ bool team_next(LaneShared<NT> &S, TeamLane *tl) {
 // of a lane on the same XCD.  is_init: (re)start the lane's channel and write frame 0.
 // Between frames the lane's state is held in registers by every thread (LaneCtx, all values
 // uniform); a general or heavy frame gets it through LDS.
+// Readouts of snapshots run beside this kernel, on compute units that are full of lanes: of the 512
+// vector registers of a SIMD lane the four wavefronts that a unit's lanes have there take 4 * 112 (the
+// attribute counts pairs), and the readout kernels make do with the other 64.  For the same reason
+// nothing here goes to scratch memory (while a kernel with scratch runs, kernels of another
+// queue did not start before its first workgroups ended: 500 online streams got the first of 16
+// partial results after 8.7 of 11.4 ms; now after 1.1).  Two things hold both: the three forms of
+// a frame are inlined, and each takes the thread number and the decoder's description anew
+// (asm volatile), so that nothing derived from them is computed before the frame loop and kept.
 template <int NT, bool TEAM>
-__global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, const DecDev *Dg, const LaneParam *__restrict__ lanes, int is_init, int n_lanes, int n_lanes8,
+__global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) __attribute__((amdgpu_num_vgpr(56))) k_advance(DecDev D, const DecDev *Dg, const LaneParam *__restrict__ lanes, int is_init, int n_lanes, int n_lanes8,
                                                                    uint32_t launch) {
   LaneShared<NT> &S = lane_lds<NT, TEAM>();
   const int tid = threadIdx.x;
   const bool member = TEAM && (int)blockIdx.x >= n_lanes8;          // an extra workgroup of a lane
-  const int my_lane = uni(member ? ((int)blockIdx.x - n_lanes8) % n_lanes8 : (int)blockIdx.x);
+  int my_lane = uni(member ? ((int)blockIdx.x - n_lanes8) % n_lanes8 : (int)blockIdx.x);
   if (TEAM && my_lane >= n_lanes) return;
   TeamLane *const tl = D.teams + my_lane;
   if (tid == 0) S.team = TeamCtx{tl, 0, 1, 0u, D.team_spin_limit, 0u, 0u, 0u, 0u};
   if (TEAM && member && !team_join<NT>(S, tl, launch)) return;
+  asm volatile("" : "+s"(my_lane));                  // (the branch above meets here: without this what follows would be taken to depend on the thread)
   LaneParam lp = lanes[my_lane];
-  lp.ll = (const float *)(__attribute__((address_space(1))) const float *)uni((unsigned long long)lp.ll); lp.chan = uni(lp.chan); lp.n_frames = uni(lp.n_frames); lp.stride = uni(lp.stride);
+  lp.ll = uni(lp.ll); lp.chan = uni(lp.chan); lp.n_frames = uni(lp.n_frames); lp.stride = uni(lp.stride);
   lp.snap_every = uni(lp.snap_every); lp.snap_id0 = uni(lp.snap_id0); lp.n_snaps = uni(lp.n_snaps);
   ChanState *cs = D.chan + lp.chan;
   long long *foff = D.frame_off + (size_t)lp.chan * (size_t)(D.max_frames + 2);
@@ -198,8 +207,10 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) k_advance(DecDev D, con
       if (pos >= 0) {
         LatRec *out = D.blk_recs + (size_t)slot * (size_t)D.blk_cap + (size_t)pos;
         const long long first = ctx.lat_pos >= n ? ctx.lat_pos - n : ctx.lat_pos - n + D.lat_cap;
-        constexpr int U = 8;                            // records per thread in flight: the arc-id gathers are HBM round trips
-        for (long long i0 = tid; i0 < n; i0 += (long long)NT * U) {
+        int mine = tid;
+        asm volatile("" : "+v"(mine));                  // (computed here, not held in registers from the kernel's start)
+        constexpr int U = 4;                            // records per thread in flight: the arc-id gathers are HBM round trips
+        for (long long i0 = mine; i0 < n; i0 += (long long)NT * U) {
           LatInt r[U];
           uint32_t arc_id[U];
           // loads are unconditional (a lane past the end re-reads the last record) so that all of a
@@ -396,10 +407,8 @@ __device__ __forceinline__ ChanView chan_view(const DecDev &D, int ch, long long
   return ChanView{sp->status, sp->num_frames, sp->hist_used, sp->lat_total};
 }
 
-// W threads work on one channel (a whole wave, or a single thread).
-template <int W>
 __device__ __forceinline__ bool path_start(const DecDev &D, int ch, int use_final, const ChanView &cv, PathOut &po, int &F, int &cur) {
-  const int lane = threadIdx.x % W;
+  const int lane = threadIdx.x;
   const long long *foff = D.frame_off + (size_t)ch * (size_t)(D.max_frames + 2);
   const HTok *hist = D.hist + (size_t)ch * (size_t)D.hist_cap;
   const uint32_t *rec = D.g.rec;
@@ -410,16 +419,16 @@ __device__ __forceinline__ bool path_start(const DecDev &D, int ch, int use_fina
   const int n = (int)(foff[F + 1] - o);
   unsigned long long bf = ~0ull, bn = ~0ull; int bfi = -1, bni = -1;
   constexpr int PU = 4;                        // tokens in flight (a lane past the end looks at the last one again)
-  for (int i0 = lane; i0 < n; i0 += W * PU) {
+  for (int i0 = lane; i0 < n; i0 += 64 * PU) {
     HTok t[PU]; float fc[PU];
 #pragma unroll
-    for (int u = 0; u < PU; ++u) t[u] = hist[o + min(i0 + u * W, n - 1)];
+    for (int u = 0; u < PU; ++u) t[u] = hist[o + min(i0 + u * 64, n - 1)];
 #pragma unroll
     for (int u = 0; u < PU; ++u) fc[u] = use_final ? __uint_as_float(rec[3 * (size_t)(t[u].handle & HMASK) + 2]) : INFINITY;
 #pragma unroll
     for (int u = 0; u < PU; ++u) {
       const uint32_t h = t[u].handle & HMASK;
-      const int i = min(i0 + u * W, n - 1);
+      const int i = min(i0 + u * 64, n - 1);
       const unsigned long long kn = pack(okey(t[u].cost), h);
       if (kn < bn) { bn = kn; bni = i; }
       if (fc[u] != INFINITY) {
@@ -428,7 +437,7 @@ __device__ __forceinline__ bool path_start(const DecDev &D, int ch, int use_fina
       }
     }
   }
-  for (int d = W / 2; d; d >>= 1) {
+  for (int d = 32; d; d >>= 1) {
     unsigned long long o2 = __shfl_xor(bn, d, 64); int i2 = __shfl_xor(bni, d, 64);
     if (o2 < bn) { bn = o2; bni = i2; }
     o2 = __shfl_xor(bf, d, 64); i2 = __shfl_xor(bfi, d, 64);
@@ -452,7 +461,7 @@ __global__ void __launch_bounds__(64) k_best_path(DecDev D, const int32_t *chans
   PathOut po{0, 0, 0, 0, 0.f, 0, 0};
   int F = 0, cur = 0;
   const ChanView cv = chan_view(D, ch, snap_id);
-  const bool ok = path_start<64>(D, ch, use_final, cv, po, F, cur);
+  const bool ok = path_start(D, ch, use_final, cv, po, F, cur);
   if (threadIdx.x != 0) return;
   if (!ok) { out[blockIdx.x] = po; return; }
   int32_t *wout = words ? words + (size_t)blockIdx.x * words_cap : nullptr;
@@ -476,7 +485,7 @@ __global__ void __launch_bounds__(64) k_best_path(DecDev D, const int32_t *chans
   out[blockIdx.x] = po;
 }
 
-// Best-path words of many channels, W threads each.  Back-pointers are unique, so two best
+// Best-path words of many channels, one wave each.  Back-pointers are unique, so two best
 // paths that share a token share everything before it: each channel remembers, per frame,
 // the token through which its last traced path entered the frame and the words up to there;
 // a new trace walks back only until it meets the remembered path (a chunk of frames plus the
@@ -486,27 +495,21 @@ __global__ void __launch_bounds__(64) k_best_path(DecDev D, const int32_t *chans
 // made two more round trips per frame; 500 channels beside a decode kernel: 0.70 ms per readout.)
 // Words go to words + po.word_off: gi * words_cap, or, if words_used is given, packed (allotted
 // with one atomic add).
-// W = 64: one wave per channel (fastest when the GPU is otherwise idle).  W = 16: 125 waves for
-// 500 channels, which still find room on the compute units that hold a single lane of a running
-// decode kernel.
-template <int W>
-__global__ void __launch_bounds__(64) k_best_path_words(DecDev D, const int32_t *chans, int n_ch, int use_final, long long snap_id,
+// One wave per channel, of at most 64 registers: what the lanes of a running decode kernel leave
+// free on every compute unit (see k_advance).
+__global__ void __launch_bounds__(64, 8) k_best_path_words(DecDev D, const int32_t *chans, int use_final, long long snap_id,
                                                         int32_t *words, int words_cap, unsigned long long *words_used, PathOut *out) {
-  const int gi = (int)((blockIdx.x * blockDim.x + threadIdx.x) / W);      // channel of this thread group
-  if (gi >= n_ch) return;
-  const int ch = chans[gi];
-  const int lane = threadIdx.x % W;
+  const int gi = blockIdx.x, ch = chans[gi], lane = threadIdx.x;
   ChanState *cs = D.chan + ch;
   const long long *foff = D.frame_off + (size_t)ch * (size_t)(D.max_frames + 2);
   const HTok *hist = D.hist + (size_t)ch * (size_t)D.hist_cap;
   int32_t *entry = D.pc_entry + (size_t)ch * (size_t)(D.max_frames + 2);
   int32_t *wcount = D.pc_wcount + (size_t)ch * (size_t)(D.max_frames + 2);
   int32_t *cw = D.pc_words + (size_t)ch * (size_t)D.pc_wcap;
-  auto from_first = [&](int v) { return __shfl(v, (int)(threadIdx.x & 63) & ~(W - 1), 64); };   // of this group's lanes
   PathOut po{0, 0, 0, 0, 0.f, 0, 0};
   int F = 0, cur = 0;
   const ChanView cv = chan_view(D, ch, snap_id);
-  const bool ok = path_start<W>(D, ch, use_final, cv, po, F, cur);
+  const bool ok = path_start(D, ch, use_final, cv, po, F, cur);
   if (!ok) { if (lane == 0) out[gi] = po; return; }
   int status = 0, total = 0, merge_f = 0, k = 0;
   if (lane == 0) {
@@ -545,18 +548,16 @@ __global__ void __launch_bounds__(64) k_best_path_words(DecDev D, const int32_t 
     if (status == 0 && (long long)base + 2ll * k > (long long)D.pc_wcap) status = E_CAPACITY;
     total = base + k;
   }
-  if constexpr (W > 1) {
-    status = from_first(status); total = from_first(total); merge_f = from_first(merge_f); k = from_first(k);
-    __threadfence_block();                     // (the first lane's stores, before the others read them)
-  }
+  status = uni(status); total = uni(total); merge_f = uni(merge_f); k = uni(k);
+  __threadfence_block();                       // (the first lane's stores, before the others read them)
   if (status != 0) {
     if (lane == 0) { cs->path_nf = 0; po.status = status; po.n_words = total; out[gi] = po; }
     return;
   }
-  for (int f = merge_f + 1 + lane; f <= F; f += W) wcount[f] = total - wcount[f];
+  for (int f = merge_f + 1 + lane; f <= F; f += 64) wcount[f] = total - wcount[f];
   const int base = total - k;
-  for (int j = lane; j < k; j += W) cw[base + j] = cw[D.pc_wcap - k + j];
-  if constexpr (W > 1) __threadfence_block();
+  for (int j = lane; j < k; j += 64) cw[base + j] = cw[D.pc_wcap - k + j];
+  __threadfence_block();
   long long off = (long long)gi * words_cap;
   if (lane == 0) {
     cs->path_nf = F + 1;
@@ -566,12 +567,10 @@ __global__ void __launch_bounds__(64) k_best_path_words(DecDev D, const int32_t 
     po.word_off = off;
     out[gi] = po;
   }
-  if constexpr (W > 1) {
-    po.status = from_first(po.status);
-    off = (long long)(((unsigned long long)(uint32_t)from_first((int)(off >> 32)) << 32) | (uint32_t)from_first((int)off));
-  }
+  po.status = uni(po.status);
+  off = uni(off);
   if (po.status != 0) return;
-  for (int j = lane; j < total; j += W) words[off + j] = cw[j];
+  for (int j = lane; j < total; j += 64) words[off + j] = cw[j];
 }
 
 // Tokens of one frame in the public form: state id and caller's arc id.

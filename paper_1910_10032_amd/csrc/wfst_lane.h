@@ -131,9 +131,11 @@ __device__ __forceinline__ unsigned long long uni(unsigned long long v) {
   return ((unsigned long long)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v);
 }
 __device__ __forceinline__ long long uni(long long v) { return (long long)uni((unsigned long long)v); }
+// (a row of scores: named as global memory, or what is loaded through it would be taken for generic)
+__device__ __forceinline__ const float *uni(const float *p) {
+  return (const float *)(__attribute__((address_space(1))) const float *)uni((unsigned long long)p);
+}
 __device__ __forceinline__ float uni(float v) { return __uint_as_float(uni(__float_as_uint(v))); }
-
-
 
 
 __device__ __forceinline__ uint32_t okey(float x) {
@@ -398,7 +400,8 @@ __device__ __forceinline__ int block_excl_scan(int v, int *s_wave, int &total) {
 template <int NT, class F>
 __device__ void block_select(LaneShared<NT> &S, int n, uint32_t need, uint32_t lo, uint32_t hi, F val,
                              uint32_t &theta, uint32_t &n_less, uint32_t &n_eq) {
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));            // (what depends on it is computed here, not held in registers all through the kernel)
   constexpr int PER = NBINS / NT;
   uint32_t less = 0;
   for (;;) {
@@ -439,7 +442,8 @@ __device__ void block_select(LaneShared<NT> &S, int n, uint32_t need, uint32_t l
 // values lie at or below it.  Integer counting only: the same cut whatever the thread order.
 template <int NT, class F>
 __device__ uint32_t block_histogram_cut(LaneShared<NT> &S, int n, uint32_t need, uint32_t lo, uint32_t hi, F val) {
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));            // (what depends on it is computed here, not held in registers all through the kernel)
   constexpr int PER = NBINS / NT;
   int shift = 0;
   while ((((unsigned long long)hi - lo) >> shift) >= (unsigned long long)NBINS) ++shift;
