@@ -131,8 +131,8 @@ typedef struct {
                                 (Section 3.1: small batches are bound by latency) gives every lane
                                 a team of workgroups that share its frames of thousands of tokens;
                                 smaller frames are the first workgroup's alone, and a team that is
-                                not needed for a while leaves.  At most (units / 8) / ceil(lanes / 8)
-                                workgroups per lane.  Results do not depend on it, nor on how many
+                                not needed for a while leaves.  The device's compute units are dealt
+                                out, the lanes with the most frames first.  Results do not depend on it, nor on how many
                                 of the workgroups find room on the device.  If a barrier of a team
                                 is ever given up (a member stopped for seconds) the channel stops
                                 with WFST_E_DEVICE.  (Testing aid: the environment variable

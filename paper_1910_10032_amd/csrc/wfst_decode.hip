@@ -157,19 +157,21 @@ int check_channels(wfst_decoder *d, const int32_t *channels, int32_t n, bool nee
   return 0;
 }
 
-// How many workgroups a lane gets when a call has n lanes: as many as the device has compute units
-// for, on one XCD with each other (lane i of a call runs on XCD i % 8), but no more than TEAM_MAX and
-// no more than the configuration allows (0: the library's choice).  They help with heavy frames
+// How many workgroups a call with n lanes is launched with, or 0 for one per lane: as many as the
+// device has compute units, but no more per lane than TEAM_MAX and than the configuration allows
+// (0: the library's choice).  They are dealt to the lanes in turn, on one XCD with each other (lane i
+// of a call runs on XCD i % 8); the first lanes, which have the most frames, may get one more than
+// the others (150 lanes of a wide beam, 104 of them with a second workgroup: 17.3 -> 12.2 ms).  They help with heavy frames
 // only; a lane that has had none for a while sends them away.  Where light frames are the rule they
 // still cost something (about 15 us per call to set up and take down, and 1 us per frame: the kernel
 // with teams has fewer registers to spare), so by the library's choice lanes get them only while
 // heavy frames have been seen in the decoder's last TEAM_MEMORY calls, or nothing is known yet.
-int lane_team(wfst_decoder *d, int n) {
+int team_workgroups(wfst_decoder *d, int n) {
   const wfst_config_t &c = d->cfg;
-  const int per_xcd = d->num_cus / NUM_XCDS, lanes_per_xcd = (n + NUM_XCDS - 1) / NUM_XCDS;
+  const int n8 = (n + NUM_XCDS - 1) / NUM_XCDS * NUM_XCDS;
   const int most = c.lane_workgroups == 0 ? TEAM_AUTO : std::min(c.lane_workgroups, TEAM_MAX);
-  if (c.lane_workgroups <= 1 && (c.lane_workgroups == 1 || (c.lane_threads != 0 && c.lane_threads != 1024))) return 1;
-  if (c.frame_form != 0 || n > d->team_lanes) return 1;
+  if (c.lane_workgroups <= 1 && (c.lane_workgroups == 1 || (c.lane_threads != 0 && c.lane_threads != 1024))) return 0;
+  if (c.frame_form != 0 || n > d->team_lanes) return 0;
   if (c.lane_workgroups == 0) {
     const bool over = d->have_last_advance && hipEventQuery(d->last_advance) == hipSuccess;
     (void)hipGetLastError();                           // ("not ready" is no error)
@@ -179,9 +181,10 @@ int lane_team(wfst_decoder *d, int n) {
       if (seen) d->heavy_calls = TEAM_MEMORY;
       else if (d->heavy_calls > 0) --d->heavy_calls;
     }
-    if (d->heavy_calls == 0) return 1;
+    if (d->heavy_calls == 0) return 0;
   }
-  return std::max(1, std::min(most, per_xcd / lanes_per_xcd));
+  const int all = std::min(n8 * most, d->num_cus / NUM_XCDS * NUM_XCDS);
+  return all > n8 ? all : 0;
 }
 
 // Put the lane parameters into a pinned ring and launch the lane kernel.
@@ -202,10 +205,10 @@ int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init,
   // lanes two 512-thread workgroups share a unit.  The results do not depend on the choice.
   int threads = d->cfg.lane_threads;
   if (threads == 0) threads = n <= d->num_cus ? 1024 : NT;
-  const int team = is_init ? 1 : lane_team(d, n);
-  if (team > 1) {
+  const int blocks = is_init ? 0 : team_workgroups(d, n);
+  if (blocks > 0) {
     const int n8 = (n + NUM_XCDS - 1) / NUM_XCDS * NUM_XCDS;
-    hipLaunchKernelGGL((k_advance<1024, true>), dim3(n8 * team), dim3(1024), 0, stream, d->dev, (const DecDev *)d->d_dev, params, 0, n, n8, ++d->launches);
+    hipLaunchKernelGGL((k_advance<1024, true>), dim3(blocks), dim3(1024), 0, stream, d->dev, (const DecDev *)d->d_dev, params, 0, n, n8, ++d->launches);
   } else if (threads == 1024)
     hipLaunchKernelGGL((k_advance<1024, false>), dim3(n), dim3(1024), 0, stream, d->dev, (const DecDev *)d->d_dev, params, is_init, n, n, 0u);
   else if (threads == 256)
@@ -433,7 +436,7 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
   if (!rc) rc = dev_alloc(d, &D.aux, nl * (size_t)D.auxcap);
   if (!rc) rc = dev_alloc(d, &D.dkey, nl * (size_t)D.tokcap);
   if (!rc) rc = dev_alloc(d, &D.dslot, nl * (size_t)D.tokcap);
-  d->team_lanes = c.lane_workgroups == 1 || c.frame_form != 0 ? 0 : (int)std::min<int64_t>((int64_t)nl, d->num_cus / 2);
+  d->team_lanes = c.lane_workgroups == 1 || c.frame_form != 0 ? 0 : (int)std::min<int64_t>((int64_t)nl, d->num_cus - NUM_XCDS);
   if (!rc && d->team_lanes > 0) {
     rc = dev_alloc(d, &D.teams, (size_t)d->team_lanes);
     if (!rc && hipMemset(D.teams, 0, sizeof(TeamLane) * (size_t)d->team_lanes) != hipSuccess) rc = WFST_E_DEVICE;

@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) __attribute__((amdgpu_n
     if constexpr (TEAM) {
       if (team_open) {                                // the first heavy frame: the team is whoever has joined
         if (tid == 0) {
-          const uint32_t want = gridDim.x / (uint32_t)n_lanes8 - 1u;
+          const uint32_t want = (gridDim.x - 1u - (uint32_t)my_lane) / (uint32_t)n_lanes8;
           for (uint32_t polls = 0; polls < 64u && (uint32_t)(ld64(&tl->join) & 0xFFFFu) < want; ++polls) __builtin_amdgcn_s_sleep(4);
           const uint32_t joined = team_close();
           const uint32_t xccs = ld32(&tl->xcc_mask);
