@@ -184,7 +184,8 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) __attribute__((amdgpu_n
   // the host has seen the progress words of all lanes, so nothing ever waits inside a kernel.
   int n_sealed = 0;
   auto seal = [&]() {
-    __syncthreads();                                  // every wave has issued its stores of the frames so far
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the lattice records of the frames so far are where they are read below
+    __syncthreads();
     const long long id = lp.snap_id0 + n_sealed;
     long long blk_start = 0, blk_count = 0;
     if (D.n_blk > 0 && D.lattice_on) {
@@ -249,17 +250,21 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) __attribute__((amdgpu_n
     ++n_sealed;
   };
   // a frame in the general or heavy form: the lane's state goes through LDS
+  // (every wave waits until its stores have been acknowledged: the history records of the light frame
+  // before are read by the other workgroups of the lane's team as soon as they are called)
   auto state_to_lds = [&]() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (tid == 0) {
       S.status = ctx.status; S.nf = ctx.nf; S.n_in = ctx.n_in; S.in_off = ctx.hist_used - ctx.n_in; S.hist_used = ctx.hist_used;
       S.lat_room = D.lat_cap - ctx.lat_pend; S.lat_total = ctx.lat_total; S.lat_pos = ctx.lat_pos;
     }
-    __syncthreads();                                  // (also: the light frames' history stores have arrived)
+    __syncthreads();
   };
   auto state_from_lds = [&]() {
     ctx.status = uni(S.status); ctx.nf = uni(S.nf); ctx.n_in = uni(S.n_in); ctx.hist_used = uni(S.hist_used);
     ctx.lat_pend = D.lat_cap - uni(S.lat_room); ctx.lat_total = uni(S.lat_total); ctx.lat_pos = uni(S.lat_pos);
     ctx.tok_valid = false;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the frame's history records, which the next frame starts from)
     __syncthreads();                                  // all have read the state before the next such frame rewrites it
   };
   auto run_general = [&](const float *ll) {
