@@ -90,13 +90,19 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
   LatInt *const lat = D.lat + (size_t)chan * (size_t)D.lat_cap;
   const uint32_t claim_limit = min((uint32_t)L::CLAIM_LIMIT, (uint32_t)D.tokcap);
 
-  // ---- 0. what the previous light frame left: its table entries are cleared here, beside the
-  //         first memory round trip of this frame ---------------------------------------------
-#pragma unroll 1
-  for (uint32_t i = tid; i < ctx.pending_clear; i += NT) slots[S.lq[i]] = fresh;
+  // ---- 0. what the previous light frame left: its table entries are cleared here, while this frame's
+  //         first memory round trip is under way (cleared before it: a dictation's 360 frames and
+  //         12 partial results take 3.98 instead of 3.94 ms) --------------------------------------
+  uint32_t to_clear = ctx.pending_clear;
   ctx.pending_clear = 0;
+  auto clear_table = [&]() {
+#pragma unroll 1
+    for (uint32_t i = tid; i < to_clear; i += NT) slots[S.lq[i]] = fresh;
+    to_clear = 0;
+  };
   if (nf > D.max_frames) { ctx.status = E_HISTORY_OVERFLOW; return true; }
   if (!is_init && !ctx.tok_valid) {            // the token list is not in LDS (first frame of a call, or after a general frame)
+    clear_table();
 #pragma unroll 1
     for (int w = tid; w < L::MARK_WORDS; w += NT) { mark_in[w] = make_uint2(0, 0); mark_out[w] = make_uint2(0, 0); }
     if (tid == 0) S.list_dead = 0;
@@ -137,7 +143,7 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
     lds_barrier();
   }
   const int total = is_init ? 0 : (int)ctx.n_arcs;
-  if (total > L::ARCS || (total > L::TILE && L::TILE * 5 / 4 > D.auxcap)) { ctx.tok_valid = false; __syncthreads(); return false; }   // (the barrier: the table is clear before the next light frame)
+  if (total > L::ARCS || (total > L::TILE && L::TILE * 5 / 4 > D.auxcap)) { clear_table(); ctx.tok_valid = false; __syncthreads(); return false; }   // (the barrier: the table is clear before the next light frame)
 
   PHASE_MARK(0);
   // A claimed state takes the frame's next token number, that many arc positions for the next
@@ -191,6 +197,7 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
       dw[u] = a[0]; wt[u] = __uint_as_float(a[1]); w2[u] = a[2];
     }
     __builtin_amdgcn_sched_barrier(0);         // (keeps the loads above together and their uses below them)
+    clear_table();
 #pragma unroll
     for (int u = 0; u < UA; ++u) sc[u] = ll[have[u] ? w2[u] & D.g.pdf_mask : 0u];
     __builtin_amdgcn_sched_barrier(0);
@@ -304,6 +311,7 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
       if (!put(sl, h, D.g.start_info, 0u, 0u, 0u)) C.cnt[0] |= CNT_RESTART;
     }
   } else if (!has_arcs) {
+    clear_table();
     lds_barrier();
   } else if (ua == 1) {
     first_tile(std::integral_constant<int, 1>{});
