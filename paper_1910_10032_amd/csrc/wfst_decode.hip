@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -28,6 +29,7 @@ constexpr int NT = 512;          // threads of the workgroup that owns a lane
 constexpr int TEAM_MEMORY = 8;   // calls after one with heavy frames for which lanes get teams
 constexpr int TEAM_AUTO = 8;     // workgroups of a team by the library's choice (400 frames of 42 000 arcs: 4 / 8 / 16 -> 42.9 / 32.9 / 35.2 ms)
 constexpr int NUM_XCDS = 8;      // the dispatcher deals workgroups to them in turn
+constexpr int POLL_MS = 5;       // how long a readout is polled for
 constexpr int PARAM_RING = 8;    // pinned buffers for lane parameters
 constexpr size_t PINNED_WORDS_BYTES = (size_t)16 << 20;   // best-path words of a readout that go straight to pinned host memory
 
@@ -68,18 +70,21 @@ struct wfst_decoder {
   unsigned long long *d_cnt = nullptr;
   long long *d_offs = nullptr;          // readout scratch [max(num_channels, max_lanes) + 1]
   hipStream_t last_stream = nullptr;    // stream of the last advance call; readouts use it
-  hipEvent_t last_advance = nullptr;    // recorded behind the last advance call
-  bool have_last_advance = false;
+  hipEvent_t last_advance = nullptr;    // recorded behind the last advance call (one of param_ev)
   int32_t last_lanes = 0;               // lanes of the last advance call
+  hipEvent_t last_init = nullptr;       // recorded behind the last initialisation of channels (one of param_ev),
+  bool side_waits = true;               //   for which side_stream waits already
   hipStream_t side_stream = nullptr;    // snapshot readouts run here, beside the decoding
   int32_t *h_heavy = nullptr;           // [max_lanes], in h_pinned: frames of a lane's last call that were not light
   int heavy_calls = 1;        // calls for which lanes still get teams, unless another one has such frames
+  uint32_t *h_done = nullptr, *d_done = nullptr;   // in h_pinned: number of the last readout that is over; its device address
+  uint32_t readouts = 0;                // readouts waited for so far
+  uint32_t *d_drain = nullptr;          // blocks of a drain that have finished (zero between drains)
   long long *h_sealed = nullptr;        // [max_lanes], in h_pinned: id of the last snapshot each lane sealed
   int64_t next_snap_id = 1;
   struct SnapCall { int64_t id0; int32_t n_snaps, n_lanes; hipStream_t stream; };
   std::deque<SnapCall> snap_calls;      // the advance calls that seal snapshots, newest last
   std::vector<int64_t> blk_ids;         // host mirror: snapshot id each block slot is assigned to
-  long long *d_ranges = nullptr;        // readout scratch [2 * max(num_channels, max_lanes) + 1]
   bool profiling = false;
   int num_cus = 0;                      // compute units of the device
   void *noalloc_scratch = nullptr;      // this device's copy of `scratch`
@@ -173,7 +178,7 @@ int team_workgroups(wfst_decoder *d, int n) {
   if (c.lane_workgroups <= 1 && (c.lane_workgroups == 1 || (c.lane_threads != 0 && c.lane_threads != 1024))) return 0;
   if (c.frame_form != 0 || n > d->team_lanes) return 0;
   if (c.lane_workgroups == 0) {
-    const bool over = d->have_last_advance && hipEventQuery(d->last_advance) == hipSuccess;
+    const bool over = d->last_advance && hipEventQuery(d->last_advance) == hipSuccess;
     (void)hipGetLastError();                           // ("not ready" is no error)
     if (over) {                                        // (what a call still running finds out counts later)
       int32_t seen = 0;
@@ -216,7 +221,8 @@ int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init,
   else
     hipLaunchKernelGGL((k_advance<NT, false>), dim3(n), dim3(NT), 0, stream, d->dev, (const DecDev *)d->d_dev, params, is_init, n, n, 0u);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipEventRecord(d->param_ev[slot], stream));
+  HIP_TRY(hipEventRecord(d->param_ev[slot], stream));        // (a name below whose slot comes round again waits for more than it must)
+  if (is_init) { d->last_init = d->param_ev[slot]; d->side_waits = false; } else d->last_advance = d->param_ev[slot];
   if (e0) { HIP_TRY(hipEventRecord(e1, stream)); d->prof_events.push_back({e0, e1}); }
   return 0;
 }
@@ -445,12 +451,13 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
   if (!rc) rc = dev_alloc(d, &d->d_chans, std::max(nc, nl));
   if (!rc) rc = dev_alloc(d, &d->d_pathout, std::max(nc, nl));
   if (!rc) rc = dev_alloc(d, &d->d_cnt, 1);
+  if (!rc) rc = dev_alloc(d, &d->d_drain, 1);
+  if (!rc && hipMemset(d->d_drain, 0, sizeof(uint32_t)) != hipSuccess) rc = WFST_E_DEVICE;
 #ifdef WFST_PHASE_TIMING
   if (!rc) rc = dev_alloc(d, &D.dbg, 8 + 16384);
   if (!rc && hipMemset(D.dbg, 0, 8 * (8 + 16384)) != hipSuccess) rc = WFST_E_DEVICE;
 #endif
   if (!rc) rc = dev_alloc(d, &d->d_offs, std::max(nc, nl) + 1);
-  if (!rc) rc = dev_alloc(d, &d->d_ranges, 2 * std::max(nc, nl) + 1);
   if (!rc && c.lattice_on) {
     rc = dev_alloc(d, &d->fl_te, nc * (size_t)D.hist_cap);
     if (!rc) rc = dev_alloc(d, &d->fl_rs, nc * (size_t)(c.max_frames + 3));
@@ -468,7 +475,7 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
     // one pinned allocation: the ring of lane parameters, then the lanes' progress words
     const size_t ring_bytes = PARAM_RING * sizeof(LaneParam) * nl;
     void *pinned_dev = nullptr;
-    ok = ok && hipHostMalloc(&d->h_pinned, ring_bytes + (sizeof(long long) + sizeof(int32_t)) * nl) == hipSuccess &&
+    ok = ok && hipHostMalloc(&d->h_pinned, ring_bytes + (sizeof(long long) + sizeof(int32_t)) * nl + sizeof(uint32_t)) == hipSuccess &&
          hipHostGetDevicePointer(&pinned_dev, d->h_pinned, 0) == hipSuccess;
     for (int i = 0; ok && i < PARAM_RING; ++i) {
       d->h_params[i] = (LaneParam *)d->h_pinned + (size_t)i * nl;
@@ -477,7 +484,6 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
     }
     ok = ok && hipMemset(D.snap, 0, sizeof(ChanSnap) * nc * SNAP_RING) == hipSuccess &&
          hipStreamCreateWithFlags(&d->side_stream, hipStreamNonBlocking) == hipSuccess &&
-         hipEventCreateWithFlags(&d->last_advance, hipEventDisableTiming) == hipSuccess &&
          ensure_pinned(d, (sizeof(long long) + sizeof(LatticeInfoDev)) * (std::max(nc, nl) + 1)) == 0;   // (what no call grows)
     if (ok) {
       d->h_sealed = (long long *)((char *)d->h_pinned + ring_bytes);
@@ -486,6 +492,9 @@ int wfst_decode_create(const wfst_graph_t *graph, const wfst_config_t *config, w
       d->h_heavy = (int32_t *)(d->h_sealed + nl);
       D.lane_heavy = (int32_t *)(D.lane_sealed + nl);
       std::memset(d->h_heavy, 0, sizeof(int32_t) * nl);
+      d->h_done = (uint32_t *)(d->h_heavy + nl);
+      d->d_done = (uint32_t *)(D.lane_heavy + nl);
+      *d->h_done = 0;
     }
     ok = ok && hipMalloc((void **)&d->d_dev, sizeof(DecDev)) == hipSuccess && hipMemcpy(d->d_dev, &D, sizeof(DecDev), hipMemcpyHostToDevice) == hipSuccess;
     if (ok) {
@@ -512,7 +521,6 @@ void wfst_decode_destroy(wfst_decoder_t *d) {
   }
   for (auto &p : d->prof_events) { (void)hipEventDestroy(p.first); (void)hipEventDestroy(p.second); }
   if (d->side_stream) (void)hipStreamDestroy(d->side_stream);
-  if (d->last_advance) (void)hipEventDestroy(d->last_advance);
   if (d->h_pinned) (void)hipHostFree(d->h_pinned);
   delete d;
 }
@@ -529,17 +537,16 @@ int wfst_decode_init_channels(wfst_decoder_t *d, const int32_t *channels, int32_
   if (!d || n < 0) return WFST_E_INVALID_ARG;
   int rc = check_channels(d, channels, n, false);
   if (rc) return rc;
-  HIP_TRY(hipStreamSynchronize(d->last_stream));      // earlier work on these channels must be over
-  HIP_TRY(hipStreamSynchronize(d->side_stream));
+  // (behind the decoder's earlier work on the stream of its last call, and nobody waits: what comes next
+  // is queued behind it, or waits for the event)
   std::vector<LaneParam> lp;
   for (int32_t i = 0; i < n; i += d->cfg.max_lanes) {
     const int32_t m = std::min(d->cfg.max_lanes, n - i);
     lp.clear();
     for (int32_t k = 0; k < m; ++k) lp.push_back(LaneParam{nullptr, channels[i + k], 1, 0, 0, 0, 0, 0});
-    rc = launch_lanes(d, lp, 1, nullptr);
+    rc = launch_lanes(d, lp, 1, d->last_stream);
     if (rc) return rc;
   }
-  HIP_TRY(hipStreamSynchronize(nullptr));
   for (int32_t i = 0; i < n; ++i) { d->inited[channels[i]] = 1; d->frames_fed[channels[i]] = 0; }
   return 0;
 }
@@ -587,8 +594,10 @@ static int advance_impl(wfst_decoder_t *d, const int32_t *channels, int32_t n_la
   std::stable_sort(lp.begin(), lp.end(), [](const LaneParam &a, const LaneParam &b) { return a.n_frames > b.n_frames; });
   // The lanes' scratch and parameter block belong to the decoder, not to the call: a call on
   // another stream than the previous one first waits for that one.
-  if (d->have_last_advance && (hipStream_t)stream != d->last_stream)
-    HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, d->last_advance, 0));
+  if ((hipStream_t)stream != d->last_stream) {
+    if (d->last_advance) HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, d->last_advance, 0));
+    if (d->last_init) HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, d->last_init, 0));
+  }
   d->last_stream = (hipStream_t)stream;
   if (n_snaps > 0 && d->dev.n_blk > 0) {     // the blocks these snapshots will fill start empty
     hipLaunchKernelGGL(k_reset_blocks, dim3((n_snaps + 63) / 64), dim3(64), 0, (hipStream_t)stream, d->dev, (long long)id0, n_snaps);
@@ -597,8 +606,6 @@ static int advance_impl(wfst_decoder_t *d, const int32_t *channels, int32_t n_la
   }
   rc = launch_lanes(d, lp, 0, (hipStream_t)stream);
   if (rc) return rc;
-  HIP_TRY(hipEventRecord(d->last_advance, (hipStream_t)stream));
-  d->have_last_advance = true;
   d->last_lanes = n_lanes;
   if (n_snaps > 0) {
     d->next_snap_id += n_snaps;
@@ -663,8 +670,28 @@ static int readout_stream(wfst_decoder *d, int64_t snap_id, hipStream_t *st) {
   if (snap_id <= 0) { *st = d->last_stream; return 0; }
   const int rc = wfst_decode_snapshot_wait(d, snap_id);
   if (rc) return rc;
+  if (!d->side_waits) { HIP_TRY(hipStreamWaitEvent(d->side_stream, d->last_init, 0)); d->side_waits = true; }
   *st = d->side_stream;
   return 0;
+}
+
+// Waits for what is queued on a readout's stream.  A kernel behind it writes the readout's number to
+// pinned host memory, where the host looks for it: 8 - 9 us for the call and wait of a kernel of 2 us,
+// 13 us with hipStreamSynchronize.  A wait that takes longer than POLL_MS goes there after all (as does
+// one that an error on the device keeps from ending).
+static int wait_for_readout(wfst_decoder *d, hipStream_t st) {
+  const uint32_t number = ++d->readouts;
+  hipLaunchKernelGGL(k_signal, dim3(1), dim3(1), 0, st, d->d_done, number);
+  HIP_TRY(hipGetLastError());
+  const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(POLL_MS);
+  do {
+    for (int i = 0; i < 256; ++i) {
+      if (__atomic_load_n(d->h_done, __ATOMIC_ACQUIRE) == number) return 0;
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() < until);
+  HIP_TRY(hipStreamSynchronize(st));
+  return __atomic_load_n(d->h_done, __ATOMIC_ACQUIRE) == number ? 0 : WFST_E_DEVICE;
 }
 
 // Copy the channel list to the device unless it is the one already there.
@@ -706,7 +733,8 @@ static int best_path_batch_impl(wfst_decoder_t *d, int64_t snap, const int32_t *
   hipLaunchKernelGGL(k_best_path_words, dim3(n), dim3(64), 0, st, d->dev, (const int32_t *)d->d_chans, use_final, sn, d_words, words_cap,
                      used_ctr, d_po);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(st));
+  rc = wait_for_readout(d, st);
+  if (rc) return rc;
   const int32_t *w = (const int32_t *)((const char *)d->h_pin + head);
   std::vector<int32_t> copied;
   if (!direct) {
@@ -848,14 +876,20 @@ int wfst_decode_lattice_arcs_batch(wfst_decoder_t *d, const int32_t *channels, i
     rc = ensure_pinned(d, sizeof(long long) * ((size_t)n + 1));
     if (rc) return rc;
   }
-  hipLaunchKernelGGL(k_lattice_offsets, dim3(1), dim3(1024), 0, st, d->dev, (const int32_t *)d->d_chans, n, d->d_offs, (long long *)d->d_pin);
-  hipLaunchKernelGGL(k_export_lattice_batch, dim3(n, 8), dim3(256), 0, st, d->dev, (const int32_t *)d->d_chans, n,
-                     (const long long *)d->d_offs, dst, (long long)cap);
-  hipLaunchKernelGGL(k_reset_lattice_batch, dim3((n + 255) / 256), dim3(256), 0, st, d->dev, (const int32_t *)d->d_chans, n,
-                     (const long long *)d->d_offs, (long long)cap);
+  if (n <= DRAIN_FEW) {
+    hipLaunchKernelGGL(k_drain_lattice_few, dim3(n, n <= 16 ? 16 : 8), dim3(256), 0, st, d->dev, (const int32_t *)d->d_chans, n, dst,
+                       (long long)cap, (long long *)d->d_pin, d->d_drain);
+  } else {
+    hipLaunchKernelGGL(k_lattice_offsets, dim3(1), dim3(1024), 0, st, d->dev, (const int32_t *)d->d_chans, n, d->d_offs, (long long *)d->d_pin);
+    hipLaunchKernelGGL(k_export_lattice_batch, dim3(n, 8), dim3(256), 0, st, d->dev, (const int32_t *)d->d_chans, n,
+                       (const long long *)d->d_offs, dst, (long long)cap);
+    hipLaunchKernelGGL(k_reset_lattice_batch, dim3((n + 255) / 256), dim3(256), 0, st, d->dev, (const int32_t *)d->d_chans, n,
+                       (const long long *)d->d_offs, (long long)cap);
+  }
   HIP_TRY(hipGetLastError());
   static_assert(sizeof(long long) == sizeof(int64_t), "offset width");
-  HIP_TRY(hipStreamSynchronize(st));
+  rc = wait_for_readout(d, st);
+  if (rc) return rc;
   std::memcpy(offsets, d->h_pin, sizeof(long long) * ((size_t)n + 1));
   const long long total = offsets[n];
   if (total > cap) return WFST_E_CAPACITY;
@@ -880,10 +914,11 @@ int wfst_decode_snapshot_lattice_arcs(wfst_decoder_t *d, int64_t snapshot_id, co
     if (rc) return rc;
   }
   hipLaunchKernelGGL(k_snapshot_ranges, dim3((std::max(n, 1) + 255) / 256), dim3(256), 0, st, d->dev, (const int32_t *)d->d_chans, n,
-                     (long long)snapshot_id, d->d_ranges);
+                     (long long)snapshot_id, (long long *)d->d_pin);    // (there is room for so many from the start)
   HIP_TRY(hipGetLastError());
-  std::vector<long long> r(2 * (size_t)n + 1);
-  HIP_TRY(copy_sync_on(st, r.data(), d->d_ranges, sizeof(long long) * r.size(), hipMemcpyDeviceToHost));
+  rc = wait_for_readout(d, st);
+  if (rc) return rc;
+  const long long *const r = (const long long *)d->h_pin;
   if (r[2 * (size_t)n] < 0) return WFST_E_NOT_INIT;
   for (int32_t i = 0; i < n; ++i) { starts[i] = r[2 * (size_t)i]; counts[i] = r[2 * (size_t)i + 1]; }
   *total = r[2 * (size_t)n];
@@ -946,7 +981,8 @@ int wfst_decode_final_lattice_batch(wfst_decoder_t *d, const int32_t *channels, 
                             d->fl_info, dst, cap);
   if (rc) return rc;
   static_assert(sizeof(long long) == sizeof(int64_t), "offset width");
-  HIP_TRY(hipStreamSynchronize(st));
+  rc = wait_for_readout(d, st);
+  if (rc) return rc;
   std::memcpy(offsets, d->h_pin, sizeof(long long) * ((size_t)n + 1));
   const LatticeInfoDev *li = (const LatticeInfoDev *)((const long long *)d->h_pin + n + 1);
   for (int32_t i = 0; i < n; ++i) { status[i] = li[i].status; fill_info(li[i], info + i); }
