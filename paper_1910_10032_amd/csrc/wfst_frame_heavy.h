@@ -456,8 +456,8 @@ __device__ __forceinline__ int heavy_frame(ConstDev *Dp, int my_lane, int chan) 
         unsigned long long *sl = reinterpret_cast<unsigned long long *>(S.hist);      // (HEAVY_LIST pairs fit the histogram's place)
         for (uint32_t i = tid; i < n; i += NT) sl[i] = sel_list[i];
         __syncthreads();
-        if ((uint32_t)tid < n) {
-          const unsigned long long v = sl[tid];
+        for (uint32_t k = tid; k < n; k += NT) {    // (HEAVY_LIST pairs are more than a workgroup of 256 threads has)
+          const unsigned long long v = sl[k];
           uint32_t rank = 0;
           for (uint32_t i = 0; i < n; ++i) rank += sl[i] < v ? 1u : 0u;
           if (rank + 1 == need) S.sel_theta = v;
