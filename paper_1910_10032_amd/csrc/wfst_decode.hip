@@ -72,8 +72,6 @@ struct wfst_decoder {
   hipStream_t last_stream = nullptr;    // stream of the last advance call; readouts use it
   hipEvent_t last_advance = nullptr;    // recorded behind the last advance call (one of param_ev)
   int32_t last_lanes = 0;               // lanes of the last advance call
-  hipEvent_t last_init = nullptr;       // recorded behind the last initialisation of channels (one of param_ev),
-  bool side_waits = true;               //   for which side_stream waits already
   hipStream_t side_stream = nullptr;    // snapshot readouts run here, beside the decoding
   int32_t *h_heavy = nullptr;           // [max_lanes], in h_pinned: frames of a lane's last call that were not light
   int heavy_calls = 1;        // calls for which lanes still get teams, unless another one has such frames
@@ -222,7 +220,7 @@ int launch_lanes(wfst_decoder *d, const std::vector<LaneParam> &lp, int is_init,
     hipLaunchKernelGGL((k_advance<NT, false>), dim3(n), dim3(NT), 0, stream, d->dev, (const DecDev *)d->d_dev, params, is_init, n, n, 0u);
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipEventRecord(d->param_ev[slot], stream));        // (a name below whose slot comes round again waits for more than it must)
-  if (is_init) { d->last_init = d->param_ev[slot]; d->side_waits = false; } else d->last_advance = d->param_ev[slot];
+  if (!is_init) d->last_advance = d->param_ev[slot];
   if (e0) { HIP_TRY(hipEventRecord(e1, stream)); d->prof_events.push_back({e0, e1}); }
   return 0;
 }
@@ -533,20 +531,42 @@ int wfst_decode_state_bytes(const wfst_decoder_t *d, int64_t *per_channel, int64
   return 0;
 }
 
+// Waits for what is queued on a readout's stream.  A kernel behind it writes the readout's number to
+// pinned host memory, where the host looks for it: 8 - 9 us for the call and wait of a kernel of 2 us,
+// 13 us with hipStreamSynchronize.  A wait that takes longer than POLL_MS goes there after all (as does
+// one that an error on the device keeps from ending).
+static int wait_for_readout(wfst_decoder *d, hipStream_t st) {
+  const uint32_t number = ++d->readouts;
+  hipLaunchKernelGGL(k_signal, dim3(1), dim3(1), 0, st, d->d_done, number);
+  HIP_TRY(hipGetLastError());
+  const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(POLL_MS);
+  do {
+    for (int i = 0; i < 256; ++i) {
+      if (__atomic_load_n(d->h_done, __ATOMIC_ACQUIRE) == number) return 0;
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() < until);
+  HIP_TRY(hipStreamSynchronize(st));
+  return __atomic_load_n(d->h_done, __ATOMIC_ACQUIRE) == number ? 0 : WFST_E_DEVICE;
+}
+
 int wfst_decode_init_channels(wfst_decoder_t *d, const int32_t *channels, int32_t n) {
   if (!d || n < 0) return WFST_E_INVALID_ARG;
   int rc = check_channels(d, channels, n, false);
   if (rc) return rc;
-  // (behind the decoder's earlier work on the stream of its last call, and nobody waits: what comes next
-  // is queued behind it, or waits for the event)
+  // (the decoder's earlier work first: the caller may free or refill what the last advance call read)
+  if (d->last_stream) HIP_TRY(hipStreamSynchronize(d->last_stream));
+  HIP_TRY(hipStreamSynchronize(d->side_stream));
   std::vector<LaneParam> lp;
   for (int32_t i = 0; i < n; i += d->cfg.max_lanes) {
     const int32_t m = std::min(d->cfg.max_lanes, n - i);
     lp.clear();
     for (int32_t k = 0; k < m; ++k) lp.push_back(LaneParam{nullptr, channels[i + k], 1, 0, 0, 0, 0, 0});
-    rc = launch_lanes(d, lp, 1, d->last_stream);
+    rc = launch_lanes(d, lp, 1, nullptr);
     if (rc) return rc;
   }
+  rc = wait_for_readout(d, nullptr);
+  if (rc) return rc;
   for (int32_t i = 0; i < n; ++i) { d->inited[channels[i]] = 1; d->frames_fed[channels[i]] = 0; }
   return 0;
 }
@@ -594,10 +614,7 @@ static int advance_impl(wfst_decoder_t *d, const int32_t *channels, int32_t n_la
   std::stable_sort(lp.begin(), lp.end(), [](const LaneParam &a, const LaneParam &b) { return a.n_frames > b.n_frames; });
   // The lanes' scratch and parameter block belong to the decoder, not to the call: a call on
   // another stream than the previous one first waits for that one.
-  if ((hipStream_t)stream != d->last_stream) {
-    if (d->last_advance) HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, d->last_advance, 0));
-    if (d->last_init) HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, d->last_init, 0));
-  }
+  if (d->last_advance && (hipStream_t)stream != d->last_stream) HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, d->last_advance, 0));
   d->last_stream = (hipStream_t)stream;
   if (n_snaps > 0 && d->dev.n_blk > 0) {     // the blocks these snapshots will fill start empty
     hipLaunchKernelGGL(k_reset_blocks, dim3((n_snaps + 63) / 64), dim3(64), 0, (hipStream_t)stream, d->dev, (long long)id0, n_snaps);
@@ -670,28 +687,8 @@ static int readout_stream(wfst_decoder *d, int64_t snap_id, hipStream_t *st) {
   if (snap_id <= 0) { *st = d->last_stream; return 0; }
   const int rc = wfst_decode_snapshot_wait(d, snap_id);
   if (rc) return rc;
-  if (!d->side_waits) { HIP_TRY(hipStreamWaitEvent(d->side_stream, d->last_init, 0)); d->side_waits = true; }
   *st = d->side_stream;
   return 0;
-}
-
-// Waits for what is queued on a readout's stream.  A kernel behind it writes the readout's number to
-// pinned host memory, where the host looks for it: 8 - 9 us for the call and wait of a kernel of 2 us,
-// 13 us with hipStreamSynchronize.  A wait that takes longer than POLL_MS goes there after all (as does
-// one that an error on the device keeps from ending).
-static int wait_for_readout(wfst_decoder *d, hipStream_t st) {
-  const uint32_t number = ++d->readouts;
-  hipLaunchKernelGGL(k_signal, dim3(1), dim3(1), 0, st, d->d_done, number);
-  HIP_TRY(hipGetLastError());
-  const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(POLL_MS);
-  do {
-    for (int i = 0; i < 256; ++i) {
-      if (__atomic_load_n(d->h_done, __ATOMIC_ACQUIRE) == number) return 0;
-      __builtin_ia32_pause();
-    }
-  } while (std::chrono::steady_clock::now() < until);
-  HIP_TRY(hipStreamSynchronize(st));
-  return __atomic_load_n(d->h_done, __ATOMIC_ACQUIRE) == number ? 0 : WFST_E_DEVICE;
 }
 
 // Copy the channel list to the device unless it is the one already there.
