@@ -40,3 +40,39 @@ def test_initialising_channels_waits_for_the_decoding(torch_cuda, B):  # noqa: F
         od = oracle.OracleDecoder(og, c.beam, c.lattice_beam, c.max_active)
         od.advance(r)
         compare_channel(dec, ch, od, frames=range(0, T + 1, 50), label=f"ch{ch}")
+
+
+@pytest.mark.parametrize("words_cap", [464, 4096])
+def test_the_first_readout_of_a_new_decoder_runs_beside_the_decoding(torch_cuda, B, words_cap):  # noqa: F811
+    """The first snapshots of an advance call of about 20 ms are sealed after less than 1 ms.  Reading
+    them grows the decoder's buffers (twice), which must not wait for the call; one later readout with
+    the buffers of both sizes, and all of them against the checker."""
+    torch = torch_cuda
+    c = synth.configs()[0]
+    g = synth.make_graph(c.graph)
+    n, T, chunk = 64, 1500, 30
+    rows = [c.loglikes(s, 0, T) for s in range(n)]
+    dec = B.WfstDecoder(B.WfstGraph(g), c.beam, c.lattice_beam, c.max_active, num_channels=n, max_lanes=n, max_frames=T,
+                        lattice_on=False)
+    chans = list(range(n))
+    dec.init_channels(chans)
+    dev = [torch.from_numpy(r).cuda() for r in rows]
+    torch.cuda.synchronize()
+    over, got = torch.cuda.Event(), []
+    with torch.cuda.stream(torch.cuda.Stream()):
+        first, _ = dec.advance(chans, dev, snapshot_every=chunk)
+        over.record()
+    for k, cap in ((0, words_cap), (1, 2 * words_cap)):
+        got.append((k, dec.best_path_batch(chans, use_final=False, words_cap=cap, snapshot=first + k)))
+        assert not over.query(), f"the readout of snapshot {k} waited for the advance call"
+    got.append((49, dec.best_path_batch(chans, use_final=False, words_cap=words_cap, snapshot=first + 49)))
+    og = oracle.OracleGraph(g)
+    for ch in (0, 1, 31, 63):
+        od = oracle.OracleDecoder(og, c.beam, c.lattice_beam, c.max_active)
+        done = 0
+        for k, res in got:
+            od.advance(rows[ch][done:(k + 1) * chunk])
+            done = (k + 1) * chunk
+            want = od.best_path(False)
+            assert res[ch]["status"] == 0 and np.array_equal(res[ch]["words"], want["words"]), f"snapshot {k} ch {ch}"
+            assert np.float32(res[ch]["total_cost"]).view(np.uint32) == np.float32(want["total_cost"]).view(np.uint32)
