@@ -198,6 +198,8 @@ class WfstDecoder:
         (device_ptr, stride) pairs together with n_frames.  With snapshot_every > 0 the lanes seal
         a snapshot after every that many frames; returns (first snapshot id, number of snapshots)."""
         ch = np.ascontiguousarray(channels, np.int32)
+        if not hasattr(loglikes, "__len__"):           # any iterable will do
+            loglikes = list(loglikes)
         assert len(loglikes) == len(ch)
         n = len(ch)
         if n >= 8 and not any([issubclass(t, tuple) for t in set(map(type, loglikes))]):
@@ -215,7 +217,7 @@ class WfstDecoder:
             else:
                 strides = np.array([p[0] if s[0] > 1 else max(p[0], s[1]) for s, p in zip(shapes, pitches)], np.int32)
             if n_frames is not None:
-                nfr = np.array(n_frames[:n], np.int32)
+                nfr = np.array([n_frames[i] for i in range(n)], np.int32)
             else:
                 nfr = np.array([s[0] for s in shapes], np.int32) if len(sizes) > 1 else np.full(n, shapes[0][0], np.int32)
         else:
