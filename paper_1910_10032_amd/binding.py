@@ -409,7 +409,8 @@ class WfstDecoder:
             names = wfst_lattice_info_t._fields_
             fields = np.frombuffer(info, np.dtype(wfst_lattice_info_t), n)
             infos = [dict(zip([k for k, _ in names], v)) for v in fields.tolist()]
-            return out[:offs[n]], offs, infos, st
+            out.resize(int(offs[n]), refcheck=False)       # (gives back what holds no record, copies nothing)
+            return out, offs, infos, st
 
     def final_lattice_device(self, channel: int, use_final: bool, out_ptr: int, cap: int, noalloc: bool = False):
         """wfst_decode_final_lattice with DEVICE output (out_ptr: device address of cap records), or its

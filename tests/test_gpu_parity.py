@@ -768,6 +768,7 @@ def test_final_lattice_batch_capacity_and_dead_channels(torch_cuda, B):
     dec, ods, _ = run_pair(torch_cuda, B, g, rows, c.beam, c.lattice_beam, c.max_active, lattice_capacity=1 << 19)
     rec, offs, infos, st = dec.final_lattice_batch([0, 1, 2], True)
     assert st.tolist() == [0, B.WFST_E_DEAD_CHANNEL, 0] and offs[2] == offs[1]
+    assert rec.base is None and len(rec) == offs[3]         # nothing holds on to a buffer of the call's capacity
     for k, ch in enumerate((0, 2)):
         one, info = dec.final_lattice(ch, True)
         got = rec[offs[ch]:offs[ch + 1]]
