@@ -32,6 +32,9 @@
  *    calls are ordered one after the other even when they are given different streams (the
  *    lanes' scratch belongs to the decoder): a call on another stream than the previous one
  *    waits for that one.  Decoders of their own do run side by side.
+ *  - A call that synchronises keeps its host core busy while it waits (as the HIP runtime's
+ *    own waits do).  Programs with more waiting threads than cores should query an event of
+ *    their own first.
  */
 #ifndef WFST_DECODE_H
 #define WFST_DECODE_H
@@ -105,7 +108,7 @@ typedef struct {
                                 cover best paths only                                       */
   int64_t snapshot_block_capacity; /* lattice arcs one block holds, all lanes of a call
                                 together; 0 = min(lattice_capacity, 4096 * max_lanes)     */
-  int32_t lane_threads;      /* threads of the workgroup that owns a lane: 512, 1024, or 0 =
+  int32_t lane_threads;      /* threads of the workgroup that owns a lane: 256, 512, 1024, or 0 =
                                 per call: 1024 if the call has no more lanes than the device
                                 has compute units, else 512.  Results do not depend on it.  */
   int32_t frame_form;        /* 0 = per frame: the LDS-resident form for frames that fit it
@@ -132,12 +135,21 @@ typedef struct {
                                 a team of workgroups that share its frames of thousands of tokens;
                                 smaller frames are the first workgroup's alone, and a team that is
                                 not needed for a while leaves.  The device's compute units are dealt
-                                out, the lanes with the most frames first.  Results do not depend on it, nor on how many
-                                of the workgroups find room on the device.  If a barrier of a team
-                                is ever given up (a member stopped for seconds) the channel stops
-                                with WFST_E_DEVICE.  (Testing aid: the environment variable
-                                WFST_DECODE_WIDE_SPIN_LIMIT, read when a decoder is created, lowers
-                                the number of polls after which a barrier is given up.)       */
+                                out, the lanes with the most frames first.  Results do not depend on
+                                it, nor on how many of the workgroups find room on the device.
+                                What it costs others: the extra workgroups of a call (by the
+                                library's choice up to seven per lane, as far as there are units)
+                                each hold a compute unit and its LDS until 64 frames after the
+                                channel's last heavy frame or its start, or to the end of the call;
+                                work on another stream may find no unit free until then.  The
+                                library's choice gives teams to the first call of a decoder (and
+                                those queued before it is over) and to the eight calls after one
+                                that had heavy frames; 1 rules them out.
+                                If a barrier of a team is ever given up (a member stopped for
+                                seconds) the channel stops with WFST_E_DEVICE.  (Testing aid: the
+                                environment variable WFST_DECODE_WIDE_SPIN_LIMIT, read when a
+                                decoder is created, lowers the number of polls after which a barrier
+                                is given up.)                                                  */
 } wfst_config_t;
 
 typedef struct { int32_t frame; uint32_t arc; float extra_cost; } wfst_lat_arc_t;
