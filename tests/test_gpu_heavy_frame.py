@@ -4,8 +4,11 @@ max-active cut, degrees and pdf ids that do not fit the arc records, and tight b
 import numpy as np
 import pytest
 
+import oracle
+import synth
 from gpu_compare import compare_channel
-from test_gpu_parity import B, F32, run_pair, torch_cuda  # noqa: F401  (fixtures)
+from test_gpu_parity import (B, F32, _check_paths, _check_snapshot_lattice, _oracle_lattice_of_frames, run_pair,  # noqa: F401
+                             torch_cuda)  # (fixtures)
 
 pytestmark = pytest.mark.gpu
 
@@ -88,3 +91,39 @@ def test_the_approximate_cut_is_the_same_in_every_form(torch_cuda, B):  # noqa: 
         got.append([np.sort(dec.tokens(0, f), order="state") for f in range(6)] + [np.sort(dec.lattice_arcs(0), order=("frame", "arc"))])
     for other in got[1:]:
         assert all(np.array_equal(a, b) for a, b in zip(got[0], other))
+
+
+@pytest.mark.parametrize("kw", [dict(lane_threads=512), dict(), dict(lane_workgroups=2), dict(lane_workgroups=16)])
+def test_snapshots_between_heavy_frames(torch_cuda, B, kw):  # noqa: F811
+    """Lanes seal a snapshot after every 7 frames of thousands of tokens (most of them written by the
+    other workgroups of the lane's team): the best paths and lattice arcs of each, read beside the
+    decoding, and the whole history afterwards."""
+    torch = torch_cuda
+    c = synth.configs()[1]
+    g = synth.make_graph(c.graph)
+    lens, chunk = [42, 30], 7
+    rows = [c.loglikes(s, 0, n) for s, n in enumerate(lens)]
+    og = oracle.OracleGraph(g)
+    step = [oracle.OracleDecoder(og, c.beam, c.lattice_beam, c.max_active) for _ in lens]
+    dec = B.WfstDecoder(B.WfstGraph(g), c.beam, c.lattice_beam, c.max_active, num_channels=2, max_lanes=2, max_frames=42,
+                        token_capacity=1 << 16, lattice_capacity=1 << 20, snapshot_blocks=6, snapshot_block_capacity=1 << 20, **kw)
+    dec.init_channels([0, 1])
+    dev = [torch.from_numpy(r).cuda() for r in rows]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        first, count = dec.advance([0, 1], dev, snapshot_every=chunk)
+    assert count == 6
+    for j in range(count):
+        for od, r in zip(step, rows):
+            if len(r) > j * chunk:
+                od.advance(r[j * chunk:(j + 1) * chunk])
+        _check_paths(dec.best_path_batch([0, 1], use_final=False, snapshot=first + j), step, False, f"snapshot {j} {kw}")
+        lo = lambda ch: min(0 if j == 0 else j * chunk + 1, lens[ch] + 1)
+        hi = lambda ch: min((j + 1) * chunk, lens[ch]) + 1
+        r, covered = _check_snapshot_lattice(dec, first + j, [0, 1], lambda ch: _oracle_lattice_of_frames(step[ch], lo(ch), hi(ch)),
+                                             f"snapshot {j} {kw}")
+        assert covered == r["total"]
+    torch.cuda.synchronize()
+    for ch, od in enumerate(step):
+        assert od.max_tokens_pre_prune > c.max_active
+        compare_channel(dec, ch, od, label=f"ch{ch} {kw}", lattice=False)

@@ -698,10 +698,11 @@ def test_two_decoders_share_a_graph_on_two_streams(torch_cuda, B):
 
 @pytest.mark.parametrize("G", [2, 5, 16])
 def test_several_workgroups_per_lane(torch_cuda, B, G):
-    """lane_workgroups > 1: the lane's workgroups work through every frame together (counters
-    and the selection's histogram in global memory, lane barriers between the stages).  Same
-    bits as one workgroup per lane: a heavy single stream (config 1: thousands of tokens,
-    max-active binding), several small streams side by side, exact ties, and the approximate cut."""
+    """lane_workgroups > 1: a team of workgroups shares the lane's frames of thousands of tokens (candidates
+    travel between them in global memory, with barriers of the team in between).  Same bits as one
+    workgroup per lane: a heavy single stream (config 1: thousands of tokens, max-active binding),
+    several small streams side by side (light frames: the first workgroup's alone), exact ties over
+    thousands of states, and the approximate cut."""
     c = synth.configs()[1]
     g = synth.make_graph(c.graph)
     rows = [c.loglikes(1, 0, 30)]
@@ -711,7 +712,7 @@ def test_several_workgroups_per_lane(torch_cuda, B, G):
     compare_channel(dec, 0, ods[0], label=f"cfg1 G={G}")
     # the approximate cut gives the same bytes with one and with several workgroups
     one = run_pair(torch_cuda, B, g, rows, c.beam, c.lattice_beam, c.max_active, token_capacity=1 << 16,
-                   lattice_capacity=1 << 21, approximate=True)[0]
+                   lattice_capacity=1 << 21, approximate=True, lane_workgroups=1)[0]
     many = run_pair(torch_cuda, B, g, rows, c.beam, c.lattice_beam, c.max_active, token_capacity=1 << 16,
                     lattice_capacity=1 << 21, approximate=True, lane_workgroups=G)[0]
     for f in (5, 17, 30):
@@ -725,35 +726,45 @@ def test_several_workgroups_per_lane(torch_cuda, B, G):
                            lattice_capacity=1 << 19, lane_workgroups=G)
     for ch, od in enumerate(ods):
         compare_channel(dec, ch, od, label=f"cfg0 G={G} ch{ch}")
-    # exact ties at the max-active cut
-    rng = np.random.default_rng(5)
-    gt = random_graph(rng, num_states=400, n_emit_per_state=(3, 6), eps_prob=0.004, num_pdfs=4, wmax=2, integer=True)
-    rt = [-rng.integers(0, 2, size=(15, 4)).astype(F32)]
-    dec, ods, _ = run_pair(torch_cuda, B, gt, rt, beam=6.0, lbeam=2.0, alpha=37, token_capacity=2048, lane_workgroups=G)
+    # exact ties at the max-active cut, in frames of more tokens than a light frame takes
+    from test_gpu_heavy_frame import layers
+    gt, rt = layers(6000, seed=5, wmax=2)
+    dec, ods, _ = run_pair(torch_cuda, B, gt, [np.round(rt[0] / 4)], beam=40.0, lbeam=2.0, alpha=3700, token_capacity=1 << 15,
+                           lattice_capacity=1 << 20, lane_workgroups=G)
+    assert ods[0].max_tokens_pre_prune >= 6000 and ods[0].max_tokens == 3700
     compare_channel(dec, 0, ods[0], label=f"ties G={G}")
 
 
 def test_a_lane_barrier_that_is_given_up_stops_the_channel_and_the_kernel_still_ends(torch_cuda, B, monkeypatch):
-    """Several workgroups per lane wait for each other a bounded number of polls.  With the bound
-    forced down to one poll (from the host: every kernel still exits normally) barriers are given
-    up: the call returns, the channel either finished correctly or stopped with WFST_E_DEVICE, and
-    a decoder created without the bound works as usual afterwards."""
-    c = synth.configs()[0]
+    """The workgroups of a team wait for each other a bounded number of polls.  With the bound forced
+    down to one poll (from the host: every kernel still exits normally) barriers are given up in the
+    first frames of thousands of tokens: the call returns, the channel has stopped with WFST_E_DEVICE
+    and holds the frames before that one, unharmed; the channel can be started again, and a decoder
+    created without the bound works as usual afterwards."""
+    c = synth.configs()[1]
     g = synth.make_graph(c.graph)
-    rows = [c.loglikes(0, 0, 40)]
+    T = 30
+    rows = [c.loglikes(0, 0, T)]
     monkeypatch.setenv("WFST_DECODE_WIDE_SPIN_LIMIT", "1")
     gg = B.WfstGraph(g)
-    dec = B.WfstDecoder(gg, c.beam, c.lattice_beam, c.max_active, num_channels=1, max_lanes=1, max_frames=40, lane_workgroups=16)
-    dec.init_channels([0])
-    dec.advance([0], [torch_cuda.from_numpy(rows[0]).cuda()])
-    torch_cuda.cuda.synchronize()
-    st = dec.stats(0)
-    assert st["status"] in (0, B.WFST_E_DEVICE)
-    if st["status"] == 0:
-        assert st["frames"] == 41
+    args = dict(token_capacity=1 << 16, lattice_capacity=1 << 21, lane_workgroups=16)
+    dec = B.WfstDecoder(gg, c.beam, c.lattice_beam, c.max_active, num_channels=1, max_lanes=1, max_frames=T, **args)
     monkeypatch.delenv("WFST_DECODE_WIDE_SPIN_LIMIT")
-    dec2, ods, _ = run_pair(torch_cuda, B, g, rows, c.beam, c.lattice_beam, c.max_active, lane_workgroups=16, lattice_capacity=1 << 19)
-    compare_channel(dec2, 0, ods[0], label="after a given-up barrier")
+    dec2, ods, _ = run_pair(torch_cuda, B, g, rows, c.beam, c.lattice_beam, c.max_active, **args)
+    compare_channel(dec2, 0, ods[0], label="without the bound")
+
+    def same_tokens(f):
+        a, b = np.sort(dec.tokens(0, f), order="state"), np.sort(dec2.tokens(0, f), order="state")
+        return np.array_equal(a, b)
+
+    for n in (T, 2):                               # until a barrier is given up; then again from the start, two light frames
+        dec.init_channels([0])
+        dec.advance([0], [torch_cuda.from_numpy(rows[0][:n]).cuda()])
+        torch_cuda.cuda.synchronize()
+        st = dec.stats(0)
+        assert (st["status"], st["frames"] <= T) == ((B.WFST_E_DEVICE, True) if n == T else (0, True))
+        assert st["frames"] == 3 or n == T
+        assert all(same_tokens(f) for f in range(st["frames"]))
 
 
 def test_final_lattice_batch_capacity_and_dead_channels(torch_cuda, B):
