@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the decoding hot path on one MI355X.
 
-Workload: benchmark configs[3] — the 8M-state / 23M-arc synthetic decoding graph,
+Workload: the 8M-state / 23M-arc synthetic decoding graph,
 500 concurrent channels fed 50-frame chunks, beam 13, max-active 7000, lattice beam 6,
 with a best-path and a lattice-arc readout for every channel after every chunk.
 

@@ -27,7 +27,9 @@ static_assert(sizeof(Slot) == 16 && sizeof(HTok) == 16 && sizeof(Aux) == 16, "16
 
 constexpr int NT = 512;          // threads of the workgroup that owns a lane
 constexpr int TEAM_MEMORY = 8;   // calls after one with heavy frames for which lanes get teams
-constexpr int TEAM_AUTO = 8;     // workgroups of a team by the library's choice (400 frames of 42 000 arcs: 4 / 8 / 16 -> 42.9 / 32.9 / 35.2 ms)
+// workgroups of a team by the library's choice (400 frames of 42 000 arcs: 1 / 4 / 8 / 16 -> 195 / 78.6 / 31.8 / 33.7 ms; the
+// tables of four are too small for most of these frames)
+constexpr int TEAM_AUTO = 8;
 constexpr int NUM_XCDS = 8;      // the dispatcher deals workgroups to them in turn
 constexpr int POLL_MS = 5;       // how long a readout is polled for
 constexpr int PARAM_RING = 8;    // pinned buffers for lane parameters
@@ -171,10 +173,11 @@ int check_channels(wfst_decoder *d, const int32_t *channels, int32_t n, bool nee
 // device has compute units, but no more per lane than TEAM_MAX and than the configuration allows
 // (0: the library's choice).  They are dealt to the lanes in turn, on one XCD with each other (lane i
 // of a call runs on XCD i % 8); the first lanes, which have the most frames, may get one more than
-// the others (150 lanes of a wide beam, 104 of them with a second workgroup: 17.3 -> 12.2 ms).  They help with heavy frames
+// the others (150 lanes of a wide beam, 104 of them with a second workgroup: 14.2 -> 9.1 ms).  They help with heavy frames
 // only; a lane that has had none for a while sends them away.  Where light frames are the rule they
 // still cost something (about 15 us per call to set up and take down, and 1 us per frame: the kernel
-// with teams has fewer registers to spare), so by the library's choice lanes get them only while
+// with teams has fewer registers to spare; 100 utterances at beam 15, 0.6 % of the frames heavy:
+// 19.4 ms without, 20.8 with them), so by the library's choice lanes get them only while
 // heavy frames have been seen in the decoder's last TEAM_MEMORY calls, or nothing is known yet.
 int team_workgroups(wfst_decoder *d, int n) {
   const wfst_config_t &c = d->cfg;

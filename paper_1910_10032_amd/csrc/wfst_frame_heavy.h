@@ -19,12 +19,19 @@
 // A frame that fills a table, a bucket or a list is given up, before anything is committed, and
 // redone by the general frame.
 //
-// What bounds it: one workgroup, the latency and the number of LDS atomics per candidate; a team,
-// about twelve barriers a frame.  A team's workgroups are laid out on one XCD (the dispatcher deals
-// workgroups to the eight XCDs in turn), whose L2 they share: a barrier then needs no write-back,
-// only stores acknowledged by the L2, an arrival count and an invalidation of the vector cache
-// (measured: 1.0 us for 8 workgroups, 1.5 us for 16, against 1.5 and 1.8 - 3.7 us with device-scope
-// release and acquire).  They check where they run; on several XCDs they use the latter.
+// What bounds it: work inside a workgroup (LDS atomics and dependent loads per candidate) more than
+// the team's barriers.  One stream of 42 000 arcs and up to 29 000 tokens per frame, team of eight,
+// 73 us a frame: closure 29 (five to seven rounds), history and lattice 14, selection 9, arcs 7,
+// insertion 5, tile lists and the barrier behind the expansion 3 each; about a dozen barriers of
+// 1.1 - 1.5 us are a fifth of it.  (One workgroup: its table is too small for most of these frames,
+// which become general: 487 us.  150 streams of 7 000 arcs: 102 us with one workgroup each, 65 with
+// a second one for 104 of them.)
+// A team's workgroups are laid out on one XCD (the dispatcher deals workgroups to the eight XCDs in
+// turn), whose L2 they share: a barrier then needs no write-back, only stores acknowledged by the
+// L2, an arrival count and an invalidation of the vector cache.  Measured with 16 bytes stored per
+// thread in front of each: 1.1 us for 8 workgroups, 1.7 us for 16; with device-scope release and
+// acquire 2.0 and 3.1 us on one XCD, 1.4 and 1.6 us on several.  They check where they run; on
+// several XCDs they use the latter.
 #pragma once
 #include "wfst_lane.h"
 
@@ -413,7 +420,7 @@ __device__ __forceinline__ int heavy_frame(ConstDev *Dp, int my_lane, int chan) 
       uint32_t loc[PER], sum = 0;
       if constexpr (TEAM) {
         uint32_t *gh = W.tl->hist[W.pass % 3], *gh_next = W.tl->hist[(W.pass + 2) % 3];
-            ++W.pass;
+        ++W.pass;
         for (int b = tid; b < NBINS; b += NT) { const uint32_t cnt = S.hist[b]; if (cnt) atomicAdd(&gh[b], cnt); }
         if (!sync()) return HEAVY_BROKEN;
 #pragma unroll

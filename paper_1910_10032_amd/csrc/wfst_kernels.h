@@ -2,29 +2,32 @@
 //
 // One workgroup owns one lane (one audio stream of the batch) for a whole advance call and
 // loops over that lane's frames by itself: streams are independent and frames are strictly
-// serial (the paper's Section 3.1), so nothing ever has to be agreed between workgroups and
-// every synchronisation is a workgroup barrier.  This takes the paper's "one CTA per
-// utterance" persistent kernel for the tail of the non-emitting iterations (Section 3.3)
-// and applies it to the entire frame: with hundreds of lanes resident the chip is filled by
-// lanes rather than by the arcs of one lane, and no kernel launch sits between the stages
-// of Fig. 1.
+// serial (the paper's Section 3.1), so lanes never wait for each other and between the stages of
+// a frame stand workgroup barriers.  This takes the paper's "one CTA per utterance" persistent
+// kernel for the tail of the non-emitting iterations (Section 3.3) and applies it to the entire
+// frame: with hundreds of lanes resident the chip is filled by lanes rather than by the arcs of
+// one lane, and no kernel launch sits between the stages of Fig. 1.  A call of so few lanes that
+// compute units would stand idle gives each lane further workgroups, a team, which share the
+// frames of thousands of tokens with the first one, with barriers of the team in between.
 //
-// Per frame (Section 3, first paragraph; Fig. 1):
+// A frame takes the first of three forms that it fits: light (everything in the LDS of one
+// workgroup, wfst_frame_light.h), heavy (state table in the LDS of one workgroup or of a team,
+// wfst_frame_heavy.h), general (any size, table in memory, wfst_frame_general.h).  What a frame
+// computes is the same in all of them (Section 3, first paragraph; Fig. 1):
 //   1. emitting expansion, load-balanced over arcs (one thread per outgoing arc, Section
-//      3.3): x = (cost + weight) - loglike[pdf]; the lane's best cost is tracked in LDS and
-//      candidates within (running best + beam) enter the lane's state table through a
-//      64-bit atomic minimum over (ordered cost bits, arc index);
-//   2. non-emitting closure: rounds over the newly added / improved tokens until a round
-//      adds nothing;
+//      3.3): x = (cost + weight) - loglike[pdf], and the lane's best cost;
+//   2. candidates within best + beam enter the lane's state table through a 64-bit atomic
+//      minimum over (ordered cost bits, arc index); then the non-emitting closure: rounds over
+//      the newly added / improved tokens until a round adds nothing;
 //   3. max-active: if more than max_active tokens are within the beam, an exact histogram
-//      selection over the ordered cost bits (then over state handles among ties) finds the
-//      cut; its cost is the frame's effective cutoff (the adaptive beam);
-//   4. contraction: the kept tokens are appended to the channel's token history, which is
-//      also the queue the next frame expands from;
+//      selection over (cost, state) finds the cut; its cost is the frame's effective cutoff
+//      (the adaptive beam);
+//   4. the kept tokens are numbered in the channel's token history, and are what the next frame
+//      expands from;
 //   5. lattice preprocessing (Section 3.4): every candidate arc that reaches a kept token
 //      within the effective cutoff and the lattice beam is recorded with its extra cost;
 //      the arc equal to the table's minimum fixes the token's back-pointer;
-//   6. the touched table slots are cleared.
+//   6. the table is cleared.
 // A call may cover many chunks of frames: at the boundaries the caller names, the lane seals
 // a snapshot of its channel (and hands its lattice records over in the caller's form) and
 // goes on, so that partial results can be read beside the decoding and no lane waits for a
@@ -90,7 +93,7 @@ __device__ __forceinline__ bool team_next(LaneShared<NT> &S, TeamLane *tl) {
 // attribute counts pairs), and the readout kernels make do with the other 64.  For the same reason
 // nothing here goes to scratch memory (while a kernel with scratch runs, kernels of another
 // queue did not start before its first workgroups ended: 500 online streams got the first of 16
-// partial results after 8.7 of 11.4 ms; now after 1.1).  Two things hold both: the three forms of
+// partial results after 8.7 of 11.4 ms; now after 1.3 of 10.9).  Two things hold both: the three forms of
 // a frame are inlined, and each takes the thread number and the decoder's description anew
 // (asm volatile), so that nothing derived from them is computed before the frame loop and kept.
 template <int NT, bool TEAM>

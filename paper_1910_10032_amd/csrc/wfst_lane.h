@@ -1,4 +1,4 @@
-// What both forms of a lane's frame share: cost keys, the state table, wavefront and workgroup
+// What the forms of a lane's frame share: cost keys, the state table, wavefront and workgroup
 // primitives, and the LDS block of a lane.
 #pragma once
 #include "wfst_device.h"
@@ -28,9 +28,6 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
   const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 15), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
   const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)v, 47), d = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
   return min(min(a, b), min(c, d));
-}
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_readlane(wave_incl_scan((int)v), 63);
 }
 // One counter update per wavefront: the lanes that call this together (same call site, any
 // subset of the wave) get consecutive indices from a single atomic add.
@@ -217,8 +214,7 @@ constexpr uint32_t AUX_EPS = 0x80000000u;  // Aux::slot flag: the record is an e
 constexpr uint32_t A_FRESH = 0x80000000u;  // epsilon out-degree not counted yet
 constexpr uint32_t A_KEPT_MAX = 0x20000000u;  // aux < A_KEPT_MAX: index of the kept token
 
-// Counters of a general frame: in LDS when one workgroup owns the lane, in global memory when
-// several do (then read with loads that bypass the vector cache).
+// Counters of a general frame (the lane's first workgroup works through it alone).
 struct GenCtr {
   // queue entries (low word) and states claimed (high word) of the frame: one 64-bit counter,
   // so that a claim takes one atomic for both
@@ -301,7 +297,7 @@ struct LaneShared {
   };
   // -- general frame: its counters, and the lane's state while such a frame runs (between light
   //    frames the state lives in registers, see LaneCtx)
-  GenCtr gen;                  // the general frame's counters (one workgroup per lane)
+  GenCtr gen;
   uint32_t sel_bin, sel_below, sel_cnt;
   int status, nf, max_pre, max_post, iters_max, n_in;
   long long in_off, hist_used, lat_room, lat_total, arcs_expanded;

@@ -46,7 +46,7 @@ def test_initialising_channels_waits_for_the_decoding(torch_cuda, B):  # noqa: F
 def test_the_first_readout_of_a_new_decoder_runs_beside_the_decoding(torch_cuda, B, words_cap):  # noqa: F811
     """The first snapshots of an advance call of about 20 ms are sealed after less than 1 ms.  Reading
     them grows the decoder's buffers (twice), which must not wait for the call; one later readout with
-    the buffers of both sizes, and all of them against the checker."""
+    the buffers of both sizes, and all of them against the oracle."""
     torch = torch_cuda
     c = synth.configs()[0]
     g = synth.make_graph(c.graph)
