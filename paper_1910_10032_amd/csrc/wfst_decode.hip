@@ -26,7 +26,10 @@ static_assert(sizeof(TokOut) == sizeof(wfst_token_t), "token layout");
 static_assert(sizeof(Slot) == 16 && sizeof(HTok) == 16 && sizeof(Aux) == 16, "16-byte records");
 
 constexpr int NT = 512;          // threads of the workgroup that owns a lane
-constexpr int TEAM_MEMORY = 8;   // calls after one with heavy frames for which lanes get teams
+// Calls after one with heavy frames for which lanes get teams.  (1, 8 and 64 are alike within 2 % at beams 15 to 18 in
+// chunks of 10 to 30 frames: heavy frames come in most calls or in none.  Teams or none, 20 streams in chunks of 10:
+// 11.1 / 10.6 ms at beam 15, 19.7 / 24.0 at 16.5, 9.2 / 26.0 at 18.)
+constexpr int TEAM_MEMORY = 8;
 // workgroups of a team by the library's choice (400 frames of 42 000 arcs: 1 / 4 / 8 / 16 -> 195 / 78.6 / 31.8 / 33.7 ms; the
 // tables of four are too small for most of these frames)
 constexpr int TEAM_AUTO = 8;
