@@ -435,7 +435,10 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
     ++iters;
     if (cv & CNT_RESTART) abort_code = 1;
   }
-  if (abort_code == 1) {                       // outgrew the LDS structures: wipe the table, the general frame redoes it
+  if (abort_code == 1) {                       // outgrew the LDS structures: wipe the table, the heavy or the general frame redoes it
+    // (Every wave has read the counters by now, not only the first one, which resets them: a wave that
+    // came late would find no request to give up, take the frame for done and be a barrier off from then on.)
+    lds_barrier();
 #pragma unroll 1
     for (int i = tid; i < L::SLOTS; i += NT) slots[i] = fresh;
     if (tid == 0) reset_ctr(C);

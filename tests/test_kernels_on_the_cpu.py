@@ -1,0 +1,31 @@
+"""GPU tests with the kernels compiled for the CPU, where the wavefronts of a workgroup can be made to run far apart between
+two barriers (on the GPU they nearly always run close together) and every access outside an allocation is caught."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+sys.path.insert(0, os.path.join(HERE, "emulated"))
+
+
+@pytest.fixture(scope="module")
+def library(tmp_path_factory):
+    import emulated_gpu
+    return emulated_gpu.build(str(tmp_path_factory.mktemp("emulated")))
+
+
+@pytest.mark.parametrize("any_order", [False, True])
+@pytest.mark.parametrize("what", [
+    # light frames that fill one of their structures: kept, or given up and redone in another form
+    ["test_gpu_light_frame.py"],
+])
+def test_kernels_on_the_cpu(library, what, any_order):
+    env = dict(os.environ, EMULATED_LIBRARY=library, PYTHONPATH=os.pathsep.join([os.path.dirname(HERE), os.path.join(HERE, "emulated")]))
+    env.pop("EMULATED_ORDER", None)
+    if any_order:
+        env["EMULATED_ORDER"] = "1"
+    run = subprocess.run([sys.executable, "-m", "pytest", "-q", "-x", "-p", "emulated_gpu", "-p", "no:cacheprovider", "-m", "gpu",
+                          os.path.join(HERE, what[0])] + what[1:], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=600)
+    assert run.returncode == 0, run.stdout[-3000:]
