@@ -119,7 +119,8 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) __attribute__((amdgpu_n
 
   const Slot fresh{~0ull, EMPTY, 0xFFFFFFFFu};
   for (int i = tid; i < LightCfg<NT>::SLOTS; i += NT) S.table[i] = fresh;
-  for (int i = tid; i < 2 * LightCfg<NT>::MARK_WORDS; i += NT) S.mark[0][i] = make_uint2(0, 0);
+  constexpr int MW = LightCfg<NT>::MARK_WORDS;
+  for (int i = tid; i < 2 * MW; i += NT) S.mark[i / MW][i % MW] = make_uint2(0, 0);
   if (tid == 0) {
     reset_ctr(S.fc[0]); reset_ctr(S.fc[1]);
     if (is_init) foff[0] = 0;
@@ -150,7 +151,7 @@ __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 2) __attribute__((amdgpu_n
   // the lane's team: set up, and open to whoever is to join
   bool team_open = false, team_here = false;        // joining is possible; there are members to call
   if (TEAM && !member) {
-    for (int i = tid; i < 3 * NBINS; i += NT) tl->hist[0][i] = 0;
+    for (int i = tid; i < 3 * NBINS; i += NT) tl->hist[i / NBINS][i % NBINS] = 0;
     if (tid == 0) {
       uint32_t xcc;
       asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));

@@ -20,6 +20,8 @@ def library(tmp_path_factory):
 @pytest.mark.parametrize("what", [
     # light frames that fill one of their structures: kept, or given up and redone in another form
     ["test_gpu_light_frame.py"],
+    # teams: the second call of a decoder starts with the histograms that the first one left
+    ["test_gpu_random_sweep.py", "-k", "test_random_heavy_frames and (0] or 4])"],
 ])
 def test_kernels_on_the_cpu(library, what, any_order):
     env = dict(os.environ, EMULATED_LIBRARY=library, PYTHONPATH=os.pathsep.join([os.path.dirname(HERE), os.path.join(HERE, "emulated")]))
