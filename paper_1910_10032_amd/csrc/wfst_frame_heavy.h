@@ -273,7 +273,7 @@ __device__ __forceinline__ int heavy_frame(ConstDev *Dp, int my_lane, int chan) 
       for (;;) {
         got = atomicCAS(&slots[sl].handle, EMPTY, h);
         if (got == EMPTY || got == h || ++tries >= HC::MAX_PROBES) break;
-        sl = (sl + 1) & mask;
+        sl = (sl + slot_step(h)) & mask;
       }
       if (got == EMPTY || got == h) {
         const unsigned long long old = atomicMin(&slots[sl].val, pack(okey(x), arc));

@@ -241,7 +241,7 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
 #pragma unroll
       for (int u = 0; u < UA; ++u) {
         if (open & (1u << u)) {
-          hs[u] = (hs[u] + 1) & mask;
+          hs[u] = (hs[u] + slot_step(dw[u] & HMASK)) & mask;
           got[u] = atomicCAS(&slots[hs[u]].handle, EMPTY, dw[u] & HMASK);
         }
       }
@@ -388,7 +388,7 @@ __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, 
         for (;;) {
           got = atomicCAS(&slots[sl].handle, EMPTY, h);
           if (got == EMPTY || got == h || ++tries >= L::MAX_PROBES) break;
-          sl = (sl + 1) & mask;
+          sl = (sl + slot_step(h)) & mask;
         }
         if (got == EMPTY || got == h) {
           const unsigned long long old = atomicMin(&slots[sl].val, pack(okey(xe), re));

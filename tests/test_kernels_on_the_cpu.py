@@ -20,6 +20,8 @@ def library(tmp_path_factory):
 @pytest.mark.parametrize("what", [
     # light frames that fill one of their structures: kept, or given up and redone in another form
     ["test_gpu_light_frame.py"],
+    # states that meet in one slot of the table
+    ["test_gpu_state_table.py"],
     # teams: the second call of a decoder starts with the histograms that the first one left
     ["test_gpu_random_sweep.py", "-k", "test_random_heavy_frames and (0] or 4])"],
 ])
