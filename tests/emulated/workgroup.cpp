@@ -30,6 +30,10 @@ namespace {
 enum { READY, WAITS, OVER };
 constexpr size_t STACK = 128 << 10;
 struct Thread { void *sp; int state, op; uint64_t v, arg, old, result; };
+struct Stacks {
+  char *base = (char *)mmap(nullptr, STACK * 1024, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  ~Stacks() { munmap(base, STACK * 1024); }
+};
 struct Workgroup { std::vector<Thread> t; void *scheduler; int current; const std::function<void()> *kernel; };
 thread_local Workgroup W;
 
@@ -70,8 +74,8 @@ void perform(int op, int a, int e) {
 }
 
 void run_workgroup(uint32_t index, dim3 grid, dim3 block, const std::function<void()> &kernel) {
-  static thread_local char *stacks = nullptr;
-  if (!stacks) stacks = (char *)mmap(nullptr, STACK * 1024, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+  static thread_local Stacks own;
+  char *const stacks = own.base;
   static thread_local uint64_t drawn = 88172645463325252ull;
   const bool any_order = getenv("EMULATED_ORDER") != nullptr;
   blockIdx = uint3{index % grid.x, index / grid.x, 0}; blockDim = uint3{block.x, 1, 1}; gridDim = uint3{grid.x, grid.y, 1};
