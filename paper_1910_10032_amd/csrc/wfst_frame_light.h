@@ -32,7 +32,7 @@
 // What bounds it: the chain of dependent steps (barriers, LDS and L2 round trips) and, with two
 // lanes on a unit, the issue of its instructions.  Measured per frame, whole calls: 1 stream on the
 // 8M-state graph at beam 13 (690 arcs a frame) 7.3 us, 300 frames on the 1000-state graph (2 270 arcs)
-// 10.4 us, 500 streams 13.6 us.  With one thread per state in the closure, a contraction step and
+// 10.4 us, 500 streams 13.2 us.  With one thread per state in the closure, a contraction step and
 // one allotment per candidate these took 12.5, 16.4 and 17.0 us.  In a build with timers (9.0 us for
 // the first): start 1.1, expansion 1.6, insertion 1.4, closure 3.0 (2.3 rounds), history and lattice 1.6.
 // A frame that outgrows the LDS structures, or meets a state whose out-degrees do not fit the
