@@ -176,6 +176,7 @@ template <bool LDS>
 __device__ __forceinline__ int ht_insert(Slot *slots, uint32_t mask, int hbits, uint32_t handle,
                                          unsigned long long K, bool &claimed, bool &improved) {
   uint32_t h = slot_hash(handle, hbits);
+  const uint32_t step = LDS ? slot_step(handle) : 1u;      // (as ht_find looks for it)
   claimed = false; improved = false;
   for (uint32_t probe = 0; probe <= mask; ++probe) {
     // one compare-and-swap tells all three cases apart: free (now ours), ours already, another state's
@@ -186,7 +187,7 @@ __device__ __forceinline__ int ht_insert(Slot *slots, uint32_t mask, int hbits, 
       improved = K < old;
       return (int)h;
     }
-    h = (h + 1) & mask;
+    h = (h + step) & mask;
   }
   return -1;
 }

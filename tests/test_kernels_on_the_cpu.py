@@ -33,3 +33,12 @@ def test_kernels_on_the_cpu(library, what, any_order):
     run = subprocess.run([sys.executable, "-m", "pytest", "-q", "-x", "-p", "emulated_gpu", "-p", "no:cacheprovider", "-m", "gpu",
                           os.path.join(HERE, what[0])] + what[1:], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=600)
     assert run.returncode == 0, run.stdout[-3000:]
+
+
+@pytest.mark.parametrize("states,bits", [(1, 4), (16, 4), (1536, 11), (2048, 11), (3072, 12)])     # to three quarters, and full
+def test_what_is_put_into_a_state_table_is_found(library, states, bits, tmp_path):
+    import emulated_gpu
+    folder, program = os.path.dirname(library), str(tmp_path / "state_table")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-w", "-I" + emulated_gpu.HERE, "-I" + os.path.join(folder, "package", "csrc"),
+                           os.path.join(emulated_gpu.HERE, "state_table.cpp"), os.path.join(emulated_gpu.HERE, "workgroup.cpp"), "-o", program, "-lpthread"])
+    assert subprocess.run([program, str(states), str(bits)]).returncode == 0
