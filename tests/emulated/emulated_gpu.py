@@ -10,6 +10,33 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 PACKAGE = os.path.join(os.path.dirname(os.path.dirname(HERE)), "paper_1910_10032_amd")
 
 
+def _converted(sources: dict) -> dict:
+    """The sources without what only the device's compiler takes.  Every rule has to find its places: a function that is
+    renamed or rewritten stops this, and does not quietly go untested."""
+    def put(pattern, by, places=None):
+        found = 0
+        for name, s in sources.items():
+            sources[name], n = re.subn(pattern, by, s)
+            found += n
+        if found != places if places else found == 0:
+            raise RuntimeError(f"{pattern}: found {found} times, expected {places or 'some'}")
+
+    put(r'asm volatile\("s_getreg_b32 %0, hwreg\(HW_REG_XCC_ID\)" : "=s"\(xcc\)\);', "xcc = 0;", 2)
+    put(r'asm volatile\("s_mov_b32 m0[^;]*;', "(void)*(const volatile uint32_t *)p;", 1)              # a load without a target
+    put(r'asm volatile\((?:[^()"]|"[^"]*"|\([^()]*\))*\);', ";")                                     # waits, and what is hidden from the compiler
+    put(r"__attribute__\(\((address_space|amdgpu_num_vgpr)\(\d+\)\)\)", "")
+    # what the lanes that happen to be here do together (the last argument: which of these places)
+    put(r"const unsigned long long m = __ballot\(1\);", "const unsigned long long m = ballot_here(1, counter);", 1)
+    put(r"__builtin_amdgcn_readlane\(\(int\)base, leader\)", "readlane_here(base, leader, counter)", 1)
+    put(r"m_all = __ballot\(1\), m_new = __ballot\(!dup\);", "m_all = ballot_here(1, &queue), m_new = ballot_here(!dup, &slots);", 1)
+    put(r"__shfl\(base, leader, 64\)", "readlane_here(base, leader, &queue)", 1)
+    for name, s in sources.items():
+        for left in ("asm volatile(", "__attribute__((a", "__ballot(1)"):
+            if left in s:
+                raise RuntimeError(f"{name}: {left} is not converted")
+    return sources
+
+
 def build(folder: str) -> str:
     """Compile copies of the sources, without the machine code in them, into a library in `folder`."""
     os.makedirs(os.path.join(folder, "package", "csrc"), exist_ok=True)
@@ -17,17 +44,11 @@ def build(folder: str) -> str:
     header = os.path.join(os.path.dirname(PACKAGE), "include", "wfst_decode.h")
     with open(header) as f, open(os.path.join(folder, "include", "wfst_decode.h"), "w") as g:
         g.write(f.read())
+    sources = {}
     for name in os.listdir(os.path.join(PACKAGE, "csrc")):
         with open(os.path.join(PACKAGE, "csrc", name)) as f:
-            s = f.read()
-        s = s.replace('asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));', "xcc = 0;")
-        s = re.sub(r'asm volatile\("s_mov_b32 m0[^;]*;', "(void)*(const volatile uint32_t *)p;", s)      # a load without a target
-        s = re.sub(r'asm volatile\((?:[^()"]|"[^"]*"|\([^()]*\))*\);', ";", s)
-        s = re.sub(r"__attribute__\(\((address_space|amdgpu_num_vgpr)\(\d+\)\)\)", "", s)
-        # what a part of a wavefront does together is done here by each thread for itself
-        s = re.sub(r"(uint32_t wave_alloc\(uint32_t \*counter\) \{).*?\n\}\n", r"\1 return atomicAdd(counter, 1u); }\n", s, flags=re.S)
-        s = s.replace("m_all = __ballot(1), m_new = __ballot(!dup);", "m_all = 1ull << (threadIdx.x & 63), m_new = dup ? 0ull : m_all;")
-        s = s.replace("base = __shfl(base, leader, 64);", "")
+            sources[name] = f.read()
+    for name, s in _converted(sources).items():
         with open(os.path.join(folder, "package", "csrc", name), "w") as g:
             g.write(s)
     out = os.path.join(folder, "libemulated.so")

@@ -1,6 +1,8 @@
 // The part of HIP that the library uses, on the CPU, for tests: a thread of a workgroup is a fiber, a workgroup that runs
-// beside others has an OS thread of its own (workgroup.cpp).  Device memory lies against inaccessible pages, so an access
-// behind the end of an allocation ends the process with the address.
+// beside others has an OS thread of its own (workgroup.cpp).  Device memory lies between inaccessible pages: against the one
+// behind it, or, with EMULATED_ORDER set, against the one in front, so that in one of the two an access outside an allocation
+// ends the process with the address (up to 15 bytes of rounding at the end excepted).  Not seen: an access that leaves its part
+// of an allocation (a lane's, a channel's) or of the workgroup's LDS for another part.
 #pragma once
 #include <math.h>
 #include <stddef.h>
@@ -65,7 +67,7 @@ EMULATED_ATOMICS(unsigned long long)
 inline void __threadfence_block() { __atomic_thread_fence(__ATOMIC_SEQ_CST); }
 
 // ---- what the threads of a wavefront or a workgroup do together --------------------------------
-enum { OP_BALLOT = 1, OP_READLANE, OP_READFIRST, OP_DPP, OP_UP, OP_XOR, OP_BARRIER, OP_SLEEP };
+enum { OP_BALLOT = 1, OP_READLANE, OP_READFIRST, OP_DPP, OP_UP, OP_XOR, OP_BARRIER, OP_SLEEP, OP_BALLOT_HERE, OP_READLANE_HERE };
 uint64_t together(int op, uint64_t v, uint64_t arg, uint64_t old = 0);
 inline unsigned long long __ballot(int p) { return together(OP_BALLOT, p ? 1 : 0, 0); }
 inline int __builtin_amdgcn_readlane(int v, int l) { return (int)together(OP_READLANE, (uint32_t)v, (uint64_t)l); }
@@ -84,6 +86,10 @@ template <class T> inline T shuffled(int op, T v, int arg) {
 template <class T> inline T __shfl(T v, int l, int) { return shuffled(OP_READLANE, v, l); }
 template <class T> inline T __shfl_up(T v, int d, int) { return shuffled(OP_UP, v, d); }
 template <class T> inline T __shfl_xor(T v, int d, int) { return shuffled(OP_XOR, v, d); }
+
+// The same for the lanes of a wavefront that have come to a place in a branch: those that wait there with the same key.
+inline unsigned long long ballot_here(int p, const void *key) { return together(OP_BALLOT_HERE, p ? 1 : 0, 0, (uint64_t)key); }
+template <class T> inline T readlane_here(T v, int l, const void *key) { return (T)together(OP_READLANE_HERE, (uint64_t)v, (uint64_t)l, (uint64_t)key); }
 
 // ---- the host's side: everything happens at once ------------------------------------------------
 typedef int hipError_t;

@@ -49,6 +49,23 @@ void entry() {
   abort();
 }
 
+// Lanes in a branch: each gets the result of those that wait for the same in the same place.
+void perform_here(int a, int e) {
+  for (int i = a; i < e; ++i) {
+    Thread &t = W.t[i];
+    if (t.state != WAITS || t.op < OP_BALLOT_HERE) continue;
+    auto beside = [&](int k) { return W.t[k].state == WAITS && W.t[k].op == t.op && W.t[k].old == t.old; };
+    t.result = 0;
+    if (t.op == OP_READLANE_HERE) {
+      if (a + (int)t.arg >= e || !beside(a + (int)t.arg)) give_up("a lane is read that is not here", a / 64);
+      t.result = W.t[a + (int)t.arg].v;
+    } else {
+      for (int k = a; k < e; ++k) if (beside(k) && W.t[k].v) t.result |= 1ull << (k - a);
+    }
+  }
+  for (int i = a; i < e; ++i) if (W.t[i].state == WAITS && W.t[i].op >= OP_BALLOT_HERE) W.t[i].state = READY;
+}
+
 // All threads of the wavefront [a, e) that are not over wait for `op`: every one gets its result.
 void perform(int op, int a, int e) {
   uint64_t mask = 0, v[64] = {};
@@ -107,7 +124,9 @@ void run_workgroup(uint32_t index, dim3 grid, dim3 block, const std::function<vo
           if (W.t[i].state == OVER) --left;
         }
         int op = 0;
-        bool slept = false;
+        bool slept = false, here = false;
+        for (int i = a; i < e; ++i) here |= W.t[i].state == WAITS && W.t[i].op >= OP_BALLOT_HERE;
+        if (here) { perform_here(a, e); continue; }
         for (int i = a; i < e; ++i) if (W.t[i].state == WAITS) {
           if (W.t[i].op == OP_SLEEP) { W.t[i].state = READY; slept = true; continue; }
           if (op != 0 && op != W.t[i].op) give_up("its threads wait for different things", w);
@@ -158,7 +177,7 @@ hipError_t hipMalloc(void **p, size_t n) {
   if (m == MAP_FAILED) return 2;
   mprotect(m, page, PROT_NONE);
   mprotect(m + length - page, page, PROT_NONE);
-  *p = m + length - page - body;
+  *p = getenv("EMULATED_ORDER") ? m + page : m + length - page - body;
   if (n <= (size_t)32 << 20) memset(*p, 0xCD, body);            // (nobody may count on zeros)
   std::lock_guard<std::mutex> lock(allocating);
   allocated[*p] = {m, length};

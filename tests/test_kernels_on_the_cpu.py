@@ -1,5 +1,7 @@
 """GPU tests with the kernels compiled for the CPU, where the wavefronts of a workgroup can be made to run far apart between
-two barriers (on the GPU they nearly always run close together) and every access outside an allocation is caught."""
+two barriers (on the GPU they nearly always run close together) and an access outside an allocation of device memory is
+caught: behind its end where the wavefronts run in their order, before its start where they run in any order.  An access that
+leaves a lane's or a channel's part of an allocation, or an array in LDS, for what lies beside it is not."""
 import os
 import subprocess
 import sys
