@@ -190,8 +190,11 @@ int wfst_decode_state_bytes(const wfst_decoder_t *decoder, int64_t *per_channel,
 /* Start (or restart) streams (Section 3.1: a channel holds the state of one audio stream
  * between batches; Section 3, first paragraph: decoding starts from the graph's start state
  * and follows chains of non-emitting arcs before the first frame): each listed channel gets
- * the start token at cost 0 and its non-emitting closure within the beam as frame 0.  channels: HOST [n], distinct, each in [0, num_channels); n may exceed
- * max_lanes (processed in groups).  Synchronises with the device before returning. */
+ * the start token at cost 0 and its non-emitting closure within the beam as frame 0.
+ * channels: HOST [n], distinct, each in [0, num_channels); n may exceed max_lanes (processed in
+ * groups).  Synchronises: returns when the channels are ready and the decoder's earlier work is
+ * over.  Its kernel runs on the default stream, so it also waits for what is queued there and
+ * on streams that synchronise with that one, other decoders' work included. */
 int wfst_decode_init_channels(wfst_decoder_t *decoder, const int32_t *channels, int32_t n);
 /* Mark channels unused (Section 3.1: a channel is released when its stream ends); their
  * buffers are reused by the next init. */

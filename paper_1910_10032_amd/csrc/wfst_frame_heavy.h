@@ -24,8 +24,9 @@
 // 73 us a frame: closure 29 (five to seven rounds), history and lattice 14, selection 9, arcs 7,
 // insertion 5, tile lists and the barrier behind the expansion 3 each; about a dozen barriers of
 // 1.1 - 1.5 us are a fifth of it.  (One workgroup: its table is too small for most of these frames,
-// which become general: 487 us.  150 streams of 7 000 arcs: 102 us with one workgroup each, 65 with
-// a second one for 104 of them, with the tables searched slot by slot; 62 now.)
+// which become general: 487 us.  150 streams of 7 000 arcs a frame, the whole call divided by the 140
+// frames of the longest (62 % of all frames are light): 102 us with one workgroup each, 65 with a second one
+// for 104 of them, with the tables searched slot by slot; 62 now.)
 // A team's workgroups are laid out on one XCD (the dispatcher deals workgroups to the eight XCDs in
 // turn), whose L2 they share: a barrier then needs no write-back, only stores acknowledged by the
 // L2, an arrival count and an invalidation of the vector cache.  Measured with 16 bytes stored per

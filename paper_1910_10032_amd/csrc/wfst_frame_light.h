@@ -35,8 +35,12 @@
 // 10.4 us, 500 streams 13.2 us.  With one thread per state in the closure, a contraction step and
 // one allotment per candidate these took 12.5, 16.4 and 17.0 us.  In a build with timers (9.0 us for
 // the first): start 1.1, expansion 1.6, insertion 1.4, closure 3.0 (2.3 rounds), history and lattice 1.6.
+// Part of the issue is moves: a kernel that holds the three forms of a frame has more uniform values
+// than scalar registers, and the compiler keeps 221 to 243 of them in lanes of vector registers (338
+// with teams); v_readlane and v_writelane are 12 to 14 % of its vector instructions (16 % with teams).
 // A frame that outgrows the LDS structures, or meets a state whose out-degrees do not fit the
-// degree info, is redone by the general frame; nothing has been committed at that point.
+// degree info, is redone in the heavy form or, where that one does not fit either, in the general
+// one; nothing has been committed at that point.
 #pragma once
 #include <type_traits>
 #include "wfst_lane.h"
@@ -61,7 +65,7 @@ __device__ __forceinline__ void count_marks(uint2 *mark, uint32_t n_arcs) {
   for (int q = 0; q < PER; ++q) { mark[lane * PER + q].y = (uint32_t)run; run += c[q]; }
 }
 
-// Returns false if the frame must be redone by the general frame.
+// Returns false if the frame must be redone in another form.
 template <int NT>
 __device__ __forceinline__ bool light_frame(const DecDev &D, LaneShared<NT> &S, LaneCtx &ctx, const float *ll, const float *ll_next,
                             bool is_init, int chan) {

@@ -162,8 +162,10 @@ __device__ __forceinline__ uint32_t slot_hash(uint32_t handle, int hbits) {
 // searches took 16.5 probes with 3000 states in 4096 slots, and the longest of the frame 58; with this
 // 7.6 and 18 (500 states in 2048: 3.8 and 3.3 for a wave).  Whole calls, slot by slot and this, us: 64 streams of a
 // wide beam with an approximate limit of 2000 11196 -> 9202, 150 of beam 18 9219 -> 8662, 100 of beam 15
-// 20706 -> 20290, 500 of beam 13 10705 -> 10559; one stream of few or of very many tokens: no difference
-// beyond that between runs.  (The table in memory, which is at most half full, is searched slot by slot.)
+// 20706 -> 20290, 500 of beam 13 10705 -> 10559; one stream of few tokens 3108 and 3136 -> 3152 and 3185 (two
+// runs of each).  One stream of very many tokens, a team of eight, is not decided: its runs come in two kinds,
+// 30.5 - 30.8 and 32.4 - 32.6 ms, and of four slot by slot one was of the second, of two with this both.
+// (The table in memory, which is at most half full, is searched slot by slot.)
 __device__ __forceinline__ uint32_t slot_step(uint32_t handle) { return ((handle * 2654435761u) >> 6) | 1u; }
 
 // Table words are read through these: in global memory with loads that bypass the per-CU
